@@ -173,7 +173,13 @@ typedef struct {
                               more than 64 entries and x is larger than 4 MiB): their arrays then
                               hold the entries ordered by (panel, row, column), the row index of an
                               entry of row i in panel p being p * nrows + i (so exports show that
-                              order), and a last pass adds each row's panel partials. */
+                              order), and a last pass adds each row's panel partials.
+                              When nothing about the kernel is asked for (csr_kernel, coo_kernel,
+                              col_panels, block_nnz, waves_per_group, lanes_per_row and
+                              rows_per_group all 0), a row has more than 64 entries and there are
+                              at least 2^19 entries over at least 32768 columns (CSR, COO, and the
+                              COO part of HYB), the product runs in two streaming passes over a
+                              second copy of the entries instead; info and exports are as above. */
 
 #define MXS_COO_AUTO 0 /* RUNS for FP32/FP16 values when no row has more than 16 entries in
                           the part, else LDS */

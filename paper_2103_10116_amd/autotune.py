@@ -94,7 +94,8 @@ def tune_batch_classes(ctx, bounds=CLASS_BOUNDS, per_class=128, tol=1e-10, cache
     return chosen
 
 
-CSR_CANDIDATES = ([dict(csr_kernel="stream", block_nnz=b) for b in (256, 512, 1024)] +
+CSR_CANDIDATES = ([dict(csr_kernel="auto")] +
+                  [dict(csr_kernel="stream", block_nnz=b) for b in (256, 512, 1024)] +
                   [dict(csr_kernel="vector", lanes_per_row=g, rows_per_group=r)
                    for g in (4, 8, 16, 32) for r in (4, 8)] +
                   [dict(csr_kernel="vector", lanes_per_row=1)] +

@@ -67,6 +67,35 @@ struct mxs_ctx {
 
 namespace mxs {
 
+// Two-pass layout of an irregular matrix's entries (binned.hip): `nbins` row
+// bins and `panels` column panels of `width` columns.  acol/aval (column
+// within the panel, its top bit set where a partial sum ends; value) are in
+// pass 1's order: panel, batch of bins, bin, row; tiles in whole runs of 8
+// entries, a panel's share of a batch in whole chunks of 64 runs; a chunk's values as
+// 16-byte words, word w of all its runs side by side.  rbase: where the
+// first partial sum of the run's tile in its chunk goes.  perm holds, in row order, the slots of the bin's
+// partial sums with the top bit set at a row's first (from run brun[b], 8 a
+// run), grank the rank within the bin of the row each run starts in, rowlist
+// the bins' non-empty rows (from brank[b]).  bent: the bins' first entries;
+// bpart, blen: their partial sums; tile_a, tile_b: first run and first
+// partial sum of each tile.  Batches of bins (batch, first partial sum
+// batch_base) have partial sums that fit the fixed scratch; work holds pass
+// 1's jobs (panel, first and past-the-last chunk): list 0 (from work_at[0])
+// for all bins, list q + 1 for batch q when there are several.
+struct BinPart {
+  int32_t *brow = nullptr, *bent = nullptr, *brank = nullptr, *bpart = nullptr,
+          *blen = nullptr, *brun = nullptr, *tile_a = nullptr, *tile_b = nullptr;
+  uint16_t* acol = nullptr;
+  void* aval = nullptr;
+  int32_t *rbase = nullptr, *rowlist = nullptr;
+  uint16_t *perm = nullptr, *grank = nullptr;
+  int4* work = nullptr;
+  std::vector<int32_t> work_at, batch, batch_base;
+  int64_t nbins = 0, parts = 0, ncols = 0;
+  int panels = 0, width = 0;
+  bool on() const { return nbins > 0; }
+};
+
 // CSR: rows partitioned into blocks of at most block_nnz entries (a row
 // longer than that is a block on its own); one wave per block.
 // CSR: either the "stream" kernel over row blocks (lanes == 0) or the
@@ -111,6 +140,9 @@ struct CsrPart {
   // zeros to whole 1024-entry chunks, so the product runs the COO chunks
   // over the panel copy (row-scaled FP16 keeps the merge kernel)
   int32_t* srow = nullptr;
+  // AUTO for irregular matrices: the two-pass product instead (no panel copy
+  // is kept; `panels` is then only what the panel rule would take)
+  BinPart bin;
 };
 
 // COO: equal chunks of block_nnz entries, one wave per chunk.  Rows cut by
@@ -137,6 +169,9 @@ struct CooPart {
   // reading those whose bit is set in pmask[i]
   int panels = 1;
   uint8_t* pmask = nullptr;
+  // AUTO for irregular matrices: the two-pass product over its own copy of
+  // the entries (the arrays above are then kept for export only)
+  BinPart bin;
 };
 
 // ELL: column-major padded slots; `waves` waves per 64 rows split the
@@ -232,7 +267,23 @@ mxs_status noalloc_scratch_init(mxs_ctx* ctx);
 void* noalloc_scratch(int device);
 mxs_status launch_spmv_scratch(mxs_ctx* ctx, const mxs_matrix* A, const void* alpha,
                                const void* x, const void* beta, void* y, const int32_t* skip,
-                               void* scratch);
+                               void* scratch, size_t bytes);
+// The two-pass product (binned.hip): whether a matrix takes it, its set-up
+// from row-ordered entries (rp: host copy of the row pointers d_rp), its
+// scratch and its launch (prod: prod_bytes of scratch, at least a batch's;
+// nv > 0: dot partials per bin as in launch_spmv_dot).
+bool bins_fit(const mxs_ctx* ctx, int64_t n, int64_t ncols, int64_t nnz, int64_t max_row,
+              mxs_dtype dt);
+mxs_status build_bins(mxs_ctx* ctx, mxs_matrix* A, BinPart& B, int64_t n, int64_t ncols,
+                      int64_t nnz, const std::vector<int32_t>& rp, const int32_t* d_rp,
+                      const int32_t* d_col, const void* d_val, mxs_dtype dt);
+mxs_status refresh_bins(mxs_ctx* ctx, BinPart& B, const int32_t* d_rp, const int32_t* d_col,
+                        const void* val, size_t vb);
+size_t bins_scratch_bytes(const BinPart& B, mxs_dtype dt);
+void launch_bins(mxs_ctx* ctx, const BinPart& B, mxs_dtype dt, const float* scale,
+                 const void* alpha, const void* x, const void* beta, void* y,
+                 const int32_t* skip, void* prod, size_t prod_bytes, double* dpart = nullptr,
+                 const void* w = nullptr, int nv = 0);
 // After the values of a CSR matrix changed in place: copies them into the
 // column-panel copy of the merge path (no-op for other kernels).  Enqueued.
 mxs_status refresh_panel_values(mxs_ctx* ctx, mxs_matrix* A);

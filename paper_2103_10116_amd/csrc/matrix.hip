@@ -653,7 +653,9 @@ mxs_status build_panels(mxs_ctx* ctx, mxs_matrix* A, int P, int C) {
 }  // namespace
 
 mxs_status refresh_panel_values(mxs_ctx* ctx, mxs_matrix* A) {
-  const CsrPart& S = A->csr;
+  CsrPart& S = A->csr;
+  if (A->fmt == MXS_CSR && S.bin.on())
+    return refresh_bins(ctx, S.bin, S.rowptr, S.col, S.val, value_bytes(A->dt));
   if (A->fmt != MXS_CSR || !S.merge || S.panels <= 1 || S.nsrows == 0) return MXS_OK;
   const int64_t W = (A->ncols + S.panels - 1) / S.panels;
   const int g = grid_for(ctx, S.nsrows, 256);
@@ -679,7 +681,15 @@ mxs_status refresh_panel_values(mxs_ctx* ctx, mxs_matrix* A) {
 
 namespace {
 
-mxs_status build_csr_merge(mxs_ctx* ctx, mxs_matrix* A, const mxs_convert_opts* opts) {
+// nothing about the product's kernel was asked for
+bool no_kernel_asked(const mxs_convert_opts* o) {
+  return !o || (o->csr_kernel == MXS_CSR_AUTO && o->coo_kernel == MXS_COO_AUTO &&
+                o->col_panels == 0 && o->block_nnz <= 0 && o->waves_per_group <= 0 &&
+                o->lanes_per_row <= 0 && o->rows_per_group <= 0);
+}
+
+mxs_status build_csr_merge(mxs_ctx* ctx, mxs_matrix* A, const mxs_convert_opts* opts,
+                           int64_t max_row) {
   if (A->dt != MXS_F64 && A->dt != MXS_F32 && A->dt != MXS_F16_ROWSCALED)
     return fail(ctx, MXS_UNSUPPORTED,
                 "the merge-path CSR kernel takes FP64, FP32 or row-scaled FP16 values");
@@ -690,6 +700,20 @@ mxs_status build_csr_merge(mxs_ctx* ctx, mxs_matrix* A, const mxs_convert_opts* 
   // 56.5 vs 58.0 us, s = 1.79 119.1 vs 119.5 us)
   A->csr.wpb = (opts && opts->waves_per_group > 1) ? 4 : 1;
   const int panels = merge_panels(A, opts);
+  if (no_kernel_asked(opts) && bins_fit(ctx, n, A->ncols, nnz, max_row, A->dt)) {
+    CsrPart& P = A->csr;
+    P.merge = true;
+    P.block_nnz = C;
+    P.nchunks = P.nblocks = (nnz + C - 1) / C;
+    P.panels = panels;
+    std::vector<int32_t> empty;
+    for (int64_t i = 0; i < n; ++i)
+      if (rp[i + 1] == rp[i]) empty.push_back((int32_t)i);
+    P.nempty = (int64_t)empty.size();
+    P.empty_rows = upload(ctx, A, empty);
+    if (!P.empty_rows) return fail(ctx, MXS_OOM, "merge-path CSR set-up");
+    return build_bins(ctx, A, P.bin, n, A->ncols, nnz, rp, P.rowptr, P.col, P.val, A->dt);
+  }
   if (panels > 1 && nnz > 0) return build_panels(ctx, A, panels, C);
   std::vector<int32_t> crow, empty;
   int64_t bad = 0;
@@ -752,10 +776,11 @@ mxs_status build_csr_partition(mxs_ctx* ctx, mxs_matrix* A, int block_nnz,
     std::vector<int32_t> crow;
     int64_t bad = 0;
     if (maxL > 64 && (A->dt == MXS_F64 || A->dt == MXS_F32 || A->dt == MXS_F16_ROWSCALED) &&
-        (merge_panels(A, opts) > 1 || merge_rows(rp, A->nnz, merge_chunk(opts), crow, &bad)))
+        (merge_panels(A, opts) > 1 ||
+         (no_kernel_asked(opts) && bins_fit(ctx, A->n, A->ncols, A->nnz, maxL, A->dt)) || merge_rows(rp, A->nnz, merge_chunk(opts), crow, &bad)))
       kind_eff = MXS_CSR_MERGE;
   }
-  if (kind_eff == MXS_CSR_MERGE) return build_csr_merge(ctx, A, opts);
+  if (kind_eff == MXS_CSR_MERGE) return build_csr_merge(ctx, A, opts, maxL);
   bool vec = kind_eff == MXS_CSR_VECTOR;
   A->csr.lanes = vec ? G : 0;
   A->csr.wpb = (opts && opts->waves_per_group == 1) ? 1 : 4;
@@ -1057,6 +1082,50 @@ mxs_status hyb_coo_panels(mxs_ctx* ctx, mxs_matrix* A, int P, const std::vector<
   return st;
 }
 
+std::vector<int32_t> empty_rows(const std::vector<int32_t>& rp, int64_t n) {
+  std::vector<int32_t> empty;
+  for (int64_t i = 0; i < n; ++i)
+    if (rp[(size_t)i + 1] == rp[(size_t)i]) empty.push_back((int32_t)i);
+  return empty;
+}
+
+// the COO format's two-pass copy from the FP64 CSR source S
+template <typename V>
+mxs_status coo_bins(mxs_ctx* ctx, const mxs_matrix* S, mxs_matrix* A, int* d_err) {
+  if (sizeof(V) == 8)
+    return build_bins(ctx, A, A->coo.bin, S->n, S->ncols, S->nnz, S->h_rowptr, S->csr.rowptr,
+                      S->csr.col, S->csr.val, A->dt);
+  void* v = ctx->alloc.alloc((size_t)S->nnz * sizeof(V) + 16);
+  if (!v) return fail(ctx, MXS_OOM, "row bins: values");
+  mxs_status st = cast_into<V>(ctx, S->nnz, (const double*)S->csr.val, v, d_err);
+  if (!st)
+    st = build_bins(ctx, A, A->coo.bin, S->n, S->ncols, S->nnz, S->h_rowptr, S->csr.rowptr,
+                    S->csr.col, v, A->dt);
+  (void)hipStreamSynchronize(ctx->stream);
+  ctx->alloc.release(v);
+  return st;
+}
+
+// the same for the hybrid's COO part (row-ordered in A->coo, values cast)
+mxs_status hyb_bins(mxs_ctx* ctx, mxs_matrix* A, const std::vector<int64_t>& off) {
+  const int64_t n = A->n;
+  std::vector<int32_t> rp((size_t)n + 1);
+  for (int64_t i = 0; i <= n; ++i) rp[(size_t)i] = (int32_t)off[(size_t)i];
+  int32_t* d_rp = (int32_t*)ctx->alloc.alloc(((size_t)n + 1) * 4);
+  mxs_status st = MXS_OK;
+  if (!d_rp)
+    st = fail(ctx, MXS_OOM, "row bins: row pointers");
+  else if (hipMemcpyAsync(d_rp, rp.data(), ((size_t)n + 1) * 4, hipMemcpyHostToDevice,
+                          ctx->stream) != hipSuccess)
+    st = fail(ctx, MXS_HIP, "copy failed");
+  else
+    st = build_bins(ctx, A, A->coo.bin, n, A->ncols, off[(size_t)n], rp, d_rp, A->coo.col,
+                    A->coo.val, A->dt);
+  (void)hipStreamSynchronize(ctx->stream);
+  ctx->alloc.release(d_rp);
+  return st;
+}
+
 template <typename V>
 mxs_status convert_typed(mxs_ctx* ctx, const mxs_matrix* S, mxs_matrix* A, mxs_format fmt,
                          const mxs_convert_opts* opts, int* d_err) {
@@ -1092,10 +1161,16 @@ mxs_status convert_typed(mxs_ctx* ctx, const mxs_matrix* S, mxs_matrix* A, mxs_f
     // large enough for the merge path's rule
     const int req = opts ? opts->col_panels : 0;
     const int P = (req > 1 || (req == 0 && Kmax > 64)) ? merge_panels(A, opts) : 1;
+    const bool bins =
+        no_kernel_asked(opts) && Kmax > 64 && bins_fit(ctx, n, S->ncols, nnz, Kmax, A->dt);
+    if (bins) {
+      if (mxs_status st = coo_bins<V>(ctx, S, A, d_err)) return st;
+    }
     if (P > 1 && nnz > 0) {
       mxs_status st = build_coo_panels<V>(ctx, S, A, P, d_err);
       if (st) return st;
-      return setup_coo_part(ctx, A, A->coo, nnz, Kmax, vb, bnnz, std::vector<int32_t>(), opts);
+      return setup_coo_part(ctx, A, A->coo, nnz, Kmax, vb, bnnz,
+                            bins ? empty_rows(hrp, n) : std::vector<int32_t>(), opts);
     }
     k_coo_rows<<<grid_for(ctx, n, 256), 256, 0, ctx->stream>>>(n, rp, A->coo.row);
     MXS_HIP_TRY(ctx, hipGetLastError());
@@ -1104,9 +1179,7 @@ mxs_status convert_typed(mxs_ctx* ctx, const mxs_matrix* S, mxs_matrix* A, mxs_f
                                       ctx->stream));
     mxs_status st = cast_into<V>(ctx, nnz, (const double*)S->csr.val, A->coo.val, d_err);
     if (st) return st;
-    std::vector<int32_t> empty;
-    for (int64_t i = 0; i < n; ++i)
-      if (hrp[i + 1] == hrp[i]) empty.push_back((int32_t)i);
+    const std::vector<int32_t> empty = empty_rows(hrp, n);
     // arrays larger than the 256 MB Infinity Cache are streamed with
     // non-temporal loads; there the default chunk is 256 entries, whose
     // kernel keeps 8 waves a SIMD (27-point 128^3: FP64 179 vs 182 us,
@@ -1183,10 +1256,13 @@ mxs_status convert_typed(mxs_ctx* ctx, const mxs_matrix* S, mxs_matrix* A, mxs_f
   // the panel partials writes every row
   const int req = opts ? opts->col_panels : 0;
   const int P = (cnnz > 0 && (req > 1 || (req == 0 && Kmax > 64))) ? merge_panels(A, opts) : 1;
+  if (no_kernel_asked(opts) && Kmax > 64 && bins_fit(ctx, n, A->ncols, cnnz, Kmax - K, A->dt)) {
+    if (mxs_status st = hyb_bins(ctx, A, off)) return st;
+  }
   if (P > 1) {
     if (mxs_status st = hyb_coo_panels<V>(ctx, A, P, off)) return st;
     return setup_coo_part(ctx, A, A->coo, cnnz, std::max<int64_t>(Kmax - K, 0), vb, bnnz,
-                          std::vector<int32_t>(), opts);
+                          A->coo.bin.on() && K == 0 ? empty : std::vector<int32_t>(), opts);
   }
   return setup_coo_part(ctx, A, A->coo, cnnz, std::max<int64_t>(Kmax - K, 0), vb, bnnz,
                         empty, opts);

@@ -27,6 +27,8 @@
 //         padding (padding is always at the end of a row).
 // HYB  -- ELL kernel for the regular part, then the COO kernel in
 //         accumulate mode for the overflow.
+// Irregular CSR, COO and HYB matrices large enough to gain from it run the
+// two-pass product of binned.hip unless a kernel was asked for.
 //
 // Per-lane sequential chains are at most NPL (+ the scan depth of 6) for
 // CSR/COO blocks and at most a quarter of a row's entries per wave for long
@@ -1548,10 +1550,34 @@ void launch_csr_merge(mxs_ctx* ctx, const mxs_matrix* A, T alpha, const T* x, T 
                                               nullptr);
 }
 
+// the two-pass product of a CSR matrix or a COO part, rows without entries
+// first (ACCUM leaves them as they are)
+template <typename V, typename T, bool ACCUM>
+void launch_binned(mxs_ctx* ctx, const BinPart& B, const float* scale, int64_t nempty,
+                   const int32_t* empty, T alpha, const T* x, T beta, T* y, const int32_t* skip,
+                   void* scratch, size_t bytes, double* dpart = nullptr, const T* w = nullptr,
+                   int nv = 0) {
+  const T b = ACCUM ? T(1) : beta;
+  if (!ACCUM && nempty > 0)
+    k_empty_rows<T><<<(unsigned)((nempty + 255) / 256), 256, 0, ctx->stream>>>(nempty, empty, y,
+                                                                             beta, skip);
+  constexpr mxs_dtype dt = std::is_same_v<V, double>  ? MXS_F64
+                           : std::is_same_v<V, float> ? MXS_F32
+                                                      : MXS_F16_ROWSCALED;
+  launch_bins(ctx, B, dt, scale, &alpha, x, &b, y, skip, scratch, bytes, dpart, w, nv);
+}
+
 template <typename V, typename T, bool SCALED>
 void launch_csr(mxs_ctx* ctx, const mxs_matrix* A, T alpha, const T* x, T beta, T* y,
-                const int32_t* skip, void* scratch) {
+                const int32_t* skip, void* scratch, size_t bytes) {
   const CsrPart& P = A->csr;
+  if (P.bin.on()) {
+    if constexpr (std::is_same_v<V, double> || std::is_same_v<V, float> ||
+                  std::is_same_v<V, _Float16>)
+      launch_binned<V, T, false>(ctx, P.bin, P.scale, P.nempty, P.empty_rows, alpha, x, beta, y,
+                                 skip, scratch, bytes);
+    return;
+  }
   if (P.merge) {
     // set-up admits FP64, FP32 and row-scaled FP16 values
     if constexpr (std::is_same_v<V, double> || std::is_same_v<V, float> ||
@@ -1654,7 +1680,13 @@ void launch_coo_chunks(mxs_ctx* ctx, const CooPart& P, T alpha, const T* x, T be
 
 template <typename V, typename T, bool ACCUM>
 void launch_coo(mxs_ctx* ctx, const CooPart& P, int64_t n, T alpha, const T* x, T beta, T* y,
-                const int32_t* skip, void* scratch) {
+                const int32_t* skip, void* scratch, size_t bytes) {
+  if (P.bin.on()) {
+    if constexpr (std::is_same_v<V, double> || std::is_same_v<V, float>)
+      launch_binned<V, T, ACCUM>(ctx, P.bin, nullptr, P.nempty, P.empty_rows, alpha, x, beta, y,
+                                 skip, scratch, bytes);
+    return;
+  }
   if (P.panels > 1) {
     // column panels: the chunks write the panel partials (scratch after the
     // continuation partials) with alpha = 1, beta = 0, the cut rows are
@@ -1719,23 +1751,23 @@ void launch_ell(mxs_ctx* ctx, const mxs_matrix* A, T alpha, const T* x, T beta, 
 
 template <typename V, typename T, bool SCALED>
 void launch_typed(mxs_ctx* ctx, const mxs_matrix* A, T alpha, const T* x, T beta, T* y,
-                  const int32_t* skip, void* scratch) {
+                  const int32_t* skip, void* scratch, size_t bytes) {
   switch (A->fmt) {
     case MXS_CSR:
-      launch_csr<V, T, SCALED>(ctx, A, alpha, x, beta, y, skip, scratch);
+      launch_csr<V, T, SCALED>(ctx, A, alpha, x, beta, y, skip, scratch, bytes);
       break;
     case MXS_COO:
-      launch_coo<V, T, false>(ctx, A->coo, A->n, alpha, x, beta, y, skip, scratch);
+      launch_coo<V, T, false>(ctx, A->coo, A->n, alpha, x, beta, y, skip, scratch, bytes);
       break;
     case MXS_ELL:
       launch_ell<V, T>(ctx, A, alpha, x, beta, y, skip);
       break;
     case MXS_HYB:
       if (A->ell.K == 0) {
-        launch_coo<V, T, false>(ctx, A->coo, A->n, alpha, x, beta, y, skip, scratch);
+        launch_coo<V, T, false>(ctx, A->coo, A->n, alpha, x, beta, y, skip, scratch, bytes);
       } else {
         launch_ell<V, T>(ctx, A, alpha, x, beta, y, skip);
-        launch_coo<V, T, true>(ctx, A->coo, A->n, alpha, x, beta, y, skip, scratch);
+        launch_coo<V, T, true>(ctx, A->coo, A->n, alpha, x, beta, y, skip, scratch, bytes);
       }
       break;
   }
@@ -1743,7 +1775,16 @@ void launch_typed(mxs_ctx* ctx, const mxs_matrix* A, T alpha, const T* x, T beta
 
 }  // namespace
 
-size_t spmv_scratch_bytes(const mxs_matrix* A) {
+namespace {
+
+const BinPart* bins_of(const mxs_matrix* A) {
+  if (A->fmt == MXS_CSR && A->csr.bin.on()) return &A->csr.bin;
+  if ((A->fmt == MXS_COO || A->fmt == MXS_HYB) && A->coo.bin.on()) return &A->coo.bin;
+  return nullptr;
+}
+
+// what the chunked product of A needs
+size_t chunk_scratch_bytes(const mxs_matrix* A) {
   int64_t chunks = 0;
   if (A->fmt == MXS_CSR && A->csr.merge) chunks = A->csr.nchunks;
   if (A->fmt == MXS_COO || A->fmt == MXS_HYB) chunks = A->coo.nchunks;
@@ -1757,29 +1798,37 @@ size_t spmv_scratch_bytes(const mxs_matrix* A) {
   return b;
 }
 
+}  // namespace
+
+size_t spmv_scratch_bytes(const mxs_matrix* A) {
+  const BinPart* B = bins_of(A);
+  return B ? bins_scratch_bytes(*B, A->dt) : chunk_scratch_bytes(A);
+}
+
 mxs_status launch_spmv_scratch(mxs_ctx* ctx, const mxs_matrix* A, const void* alpha,
                                const void* x, const void* beta, void* y, const int32_t* skip,
-                               void* scratch) {
+                               void* scratch, size_t bytes) {
   if (A->n == 0) return MXS_OK;
   if (A->dt == MXS_F64) {
     launch_typed<double, double, false>(ctx, A, *(const double*)alpha, (const double*)x,
-                                        *(const double*)beta, (double*)y, skip, scratch);
+                                        *(const double*)beta, (double*)y, skip, scratch,
+                                        bytes);
   } else if (A->dt == MXS_F32) {
     launch_typed<float, float, false>(ctx, A, *(const float*)alpha, (const float*)x,
-                                      *(const float*)beta, (float*)y, skip, scratch);
+                                      *(const float*)beta, (float*)y, skip, scratch, bytes);
   } else if (A->dt == MXS_C128) {
     using Z = cplx<double>;
     if (A->fmt != MXS_CSR) return fail(ctx, MXS_UNSUPPORTED, "complex values are CSR only");
     launch_csr<Z, Z, false>(ctx, A, *(const Z*)alpha, (const Z*)x, *(const Z*)beta, (Z*)y, skip,
-                            scratch);
+                            scratch, bytes);
   } else if (A->dt == MXS_C64) {
     using Z = cplx<float>;
     if (A->fmt != MXS_CSR) return fail(ctx, MXS_UNSUPPORTED, "complex values are CSR only");
     launch_csr<Z, Z, false>(ctx, A, *(const Z*)alpha, (const Z*)x, *(const Z*)beta, (Z*)y, skip,
-                            scratch);
+                            scratch, bytes);
   } else {
     launch_typed<_Float16, float, true>(ctx, A, *(const float*)alpha, (const float*)x,
-                                        *(const float*)beta, (float*)y, skip, scratch);
+                                        *(const float*)beta, (float*)y, skip, scratch, bytes);
   }
   MXS_HIP_TRY(ctx, hipGetLastError());
   return MXS_OK;
@@ -1828,6 +1877,14 @@ template <typename V, typename T, bool SCALED>
 int launch_dot_typed(mxs_ctx* ctx, const mxs_matrix* A, const T* x, T* y, const int32_t* skip,
                      double* dpart, void* scratch, const T* w, int nv) {
   const CsrPart& P = A->csr;
+  if (P.bin.on()) {
+    if (P.bin.nbins > kDotPartials) return 0;
+    if constexpr (std::is_same_v<V, double> || std::is_same_v<V, float> ||
+                  std::is_same_v<V, _Float16>)
+      launch_binned<V, T, false>(ctx, P.bin, P.scale, P.nempty, P.empty_rows, T(1), x, T(0), y,
+                                 skip, scratch, ctx->spmv_ws.bytes, dpart, w ? w : x, nv);
+    return (int)P.bin.nbins;
+  }
   if (P.rows_lds && P.nblocks > 0) {
     const T* wd = w ? w : x;
     if (P.block_nnz <= 512)
@@ -1854,10 +1911,10 @@ int launch_spmv_dot(mxs_ctx* ctx, const mxs_matrix* A, const void* x, void* y,
   if (A->fmt != MXS_CSR || A->n == 0 || A->n != A->ncols || nv < 1 || nv > 2) return 0;
   const CsrPart& P = A->csr;
   if (!(P.rows_lds && P.nblocks > 0) && !(P.merge && P.nchunks > 0)) return 0;
-  if (!(P.rows_lds && P.nblocks > 0) && ((w && w != x) || nv != 1)) return 0;
+  if (!P.bin.on() && !(P.rows_lds && P.nblocks > 0) && ((w && w != x) || nv != 1)) return 0;
   // the merge path without panels also keeps one dot partial per chunk
   const size_t need = spmv_scratch_bytes(A) +
-                      (P.merge && P.panels <= 1 ? (size_t)P.nchunks * sizeof(double) : 0);
+                      (P.merge && P.panels <= 1 && !P.bin.on() ? (size_t)P.nchunks * sizeof(double) : 0);
   if (need > ctx->spmv_ws.bytes) {
     if (ctx->spmv_ws.ptr) {
       if (hipStreamSynchronize(ctx->stream) != hipSuccess) return 0;
@@ -1897,7 +1954,8 @@ mxs_status launch_spmv(mxs_ctx* ctx, const mxs_matrix* A, const void* alpha, con
     ctx->spmv_ws.bytes = ctx->spmv_ws.ptr ? want : 0;
     if (!ctx->spmv_ws.ptr) return fail(ctx, MXS_OOM, "product scratch (%zu bytes)", want);
   }
-  return launch_spmv_scratch(ctx, A, alpha, x, beta, y, skip, ctx->spmv_ws.ptr);
+  return launch_spmv_scratch(ctx, A, alpha, x, beta, y, skip, ctx->spmv_ws.ptr,
+                             ctx->spmv_ws.bytes);
 }
 
 }  // namespace mxs
@@ -1918,7 +1976,9 @@ extern "C" mxs_status mxs_spmv_noalloc(mxs_ctx* ctx, const void* alpha, const mx
   if (A->device != ctx->device)
     return mxs::fail(ctx, MXS_INVALID_ARG, "matrix on device %d, ctx on device %d", A->device,
                      ctx->device);
-  const size_t need = mxs::spmv_scratch_bytes(A);
+  // (two-pass products run in as many batches of bins as the array asks for;
+  // which calls are refused goes by the chunked products' need alike)
+  const size_t need = mxs::chunk_scratch_bytes(A);
   if (need > mxs::kNoAllocScratchBytes)
     return mxs::fail(ctx, MXS_UNSUPPORTED,
                      "this product needs %zu bytes of scratch; the allocation-free product "
@@ -1926,5 +1986,6 @@ extern "C" mxs_status mxs_spmv_noalloc(mxs_ctx* ctx, const void* alpha, const mx
                      need, mxs::kNoAllocScratchBytes);
   void* p = mxs::noalloc_scratch(ctx->device);
   if (!p) return mxs::fail(ctx, MXS_HIP, "product scratch of device %d not set up", ctx->device);
-  return mxs::launch_spmv_scratch(ctx, A, alpha, x, beta, y, nullptr, p);
+  return mxs::launch_spmv_scratch(ctx, A, alpha, x, beta, y, nullptr, p,
+                                  mxs::kNoAllocScratchBytes);
 }
