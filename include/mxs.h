@@ -179,7 +179,11 @@ typedef struct {
                               rows_per_group all 0), a row has more than 64 entries and there are
                               at least 2^19 entries over at least 32768 columns (CSR, COO, and the
                               COO part of HYB), the product runs in two streaming passes over a
-                              second copy of the entries instead; info and exports are as above. */
+                              second copy of the entries instead; info and exports are as above.
+                              In the same way matrices of at least 2^17 entries on at most 64
+                              diagonals (rows of at most 64 entries, at most 255 different sets of
+                              diagonals, at most a fifth of them holes) run, in any format, over a
+                              copy of their values by diagonals without column indices. */
 
 #define MXS_COO_AUTO 0 /* RUNS for FP32/FP16 values when no row has more than 16 entries in
                           the part, else LDS */

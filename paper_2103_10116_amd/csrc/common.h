@@ -96,6 +96,24 @@ struct BinPart {
   bool on() const { return nbins > 0; }
 };
 
+// A matrix whose entries lie on D diagonals at most (stencils): its values
+// once more, in slices of 64 rows (diagonal d of row i at (i / 64 * D + d) * 64
+// + i % 64, holes 0), and which diagonals a row has as a mask that few rows
+// differ in: mask[id[i]].  Products then read one byte a row instead of a
+// column index an entry, and a slice's columns are the same shifts (off) of
+// its rows.  threes: the offsets come in threes, one apart.
+constexpr int kMaxDiags = 64, kMaxMasks = 255;
+struct DiagPart {
+  int D = 0;
+  bool threes = false;
+  int32_t lo = 0, hi = 0;    // least and largest offset
+  void* val = nullptr;
+  uint8_t* id = nullptr;     // n, padded to whole slices (rows of no diagonals)
+  uint64_t* mask = nullptr;  // 256
+  int32_t* off = nullptr;    // D offsets
+  bool on() const { return D > 0; }
+};
+
 // CSR: rows partitioned into blocks of at most block_nnz entries (a row
 // longer than that is a block on its own); one wave per block.
 // CSR: either the "stream" kernel over row blocks (lanes == 0) or the
@@ -143,6 +161,8 @@ struct CsrPart {
   // AUTO for irregular matrices: the two-pass product instead (no panel copy
   // is kept; `panels` is then only what the panel rule would take)
   BinPart bin;
+  // AUTO for matrices of few diagonals: read instead of the arrays above
+  DiagPart diag;
 };
 
 // COO: equal chunks of block_nnz entries, one wave per chunk.  Rows cut by
@@ -172,6 +192,7 @@ struct CooPart {
   // AUTO for irregular matrices: the two-pass product over its own copy of
   // the entries (the arrays above are then kept for export only)
   BinPart bin;
+  DiagPart diag;  // as for CSR
 };
 
 // ELL: column-major padded slots; `waves` waves per 64 rows split the
@@ -182,6 +203,7 @@ struct EllPart {
   int64_t K = 0;
   int64_t stride = 0;
   int waves = 1;
+  DiagPart diag;  // as for CSR
 };
 
 }  // namespace mxs

@@ -27,6 +27,8 @@
 //         padding (padding is always at the end of a row).
 // HYB  -- ELL kernel for the regular part, then the COO kernel in
 //         accumulate mode for the overflow.
+// Matrices of few diagonals (stencils) in any of these formats run k_diag over
+// a copy of their values by diagonals unless a kernel was asked for.
 // Irregular CSR, COO and HYB matrices large enough to gain from it run the
 // two-pass product of binned.hip unless a kernel was asked for.
 //
@@ -1252,8 +1254,201 @@ __global__ __launch_bounds__(64 * W) void k_ell(int64_t n, int64_t K, int64_t ld
 }
 
 // ---------------------------------------------------------------------------
+// Matrices of few diagonals (see DiagPart), any format, one lane a row and one
+// wave a slice.  Bound by memory: D values, one byte, x and y a row, where the
+// formats' own kernels read an index (two in COO) an entry as well.  27-point
+// 128^3, us (format's kernel -> this): CSR FP64 137 -> 89 (470 MB, 5.3 TB/s;
+// 64 of them the values, 15 the gathers, 10 the y stores), FP32 89 -> 46, FP16
+// 77 -> 32; COO FP64 170 -> 91; ELL FP32 86 -> 46; 7-point 128^3 CSR FP64 44 ->
+// 32 cold, 31 -> 22 from the Infinity Cache, FP16 27 -> 12.  The x of a group of three neighbouring diagonals is one load:
+// the middle one's, whose lanes hand theirs to the next lane up and down, with
+// the two that lie outside the slice read by the edge lanes.  A round's loads
+// are in flight together; no LDS (27-point FP64 96 us with a load a
+// diagonal; 98 with each row's offsets from a table in LDS).
+//
+// Each work-group takes R times 4 slices.  NV > 0: it also stores the sum of
+// w[i] * y[i] over its rows to part[blockIdx.x * NV], and with NV = 2 the sum
+// of y[i]^2 after it.
+// ---------------------------------------------------------------------------
+// v of the lane below (UP) or above; lane 0 (63) takes `edge`
+template <bool UP>
+__device__ __forceinline__ float lane_shift(float v, float edge) {
+  return __builtin_bit_cast(
+      float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, edge),
+                                         __builtin_bit_cast(int, v), UP ? 0x138 : 0x130, 0xF, 0xF,
+                                         false));
+}
+template <bool UP>
+__device__ __forceinline__ double lane_shift(double v, double edge) {
+  const uint64_t a = __builtin_bit_cast(uint64_t, v), e = __builtin_bit_cast(uint64_t, edge);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)e, (int)(uint32_t)a,
+                                                            UP ? 0x138 : 0x130, 0xF, 0xF, false);
+  const uint32_t hi =
+      (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)(e >> 32), (int)(uint32_t)(a >> 32),
+                                            UP ? 0x138 : 0x130, 0xF, 0xF, false);
+  return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+
+// U: diagonals a round; TRI: the diagonals come in threes (their offsets one
+// apart), U of these a round; FULL: whole rounds only.
+template <typename V, typename T, bool SCALED, int NV, bool NT, int U, bool TRI, bool FULL>
+__global__ __launch_bounds__(256) void k_diag(int64_t n, int64_t ncols, int R, int D, int32_t lo,
+                                              int32_t hi, const float* __restrict__ scale,
+                                              const int32_t* __restrict__ off,
+                                              const uint8_t* __restrict__ id,
+                                              const uint64_t* __restrict__ mask,
+                                              const V* __restrict__ val,
+                                              const T* __restrict__ x, T* __restrict__ y, T alpha,
+                                              T beta, const int32_t* __restrict__ skip,
+                                              const T* __restrict__ w,
+                                              double* __restrict__ part) {
+  constexpr int S = TRI ? 3 * U : U;  // slots a round
+  if (skip && *skip) return;
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t first = xcd_remap(blockIdx.x, gridDim.x) * R * 4 + wv;
+  const int64_t slices = (n + 63) / 64;
+  double d0 = 0.0, d1 = 0.0;
+  for (int64_t g = first; g < first + 4 * R && g < slices; g += 4) {
+    const int64_t i = g * 64 + lane;
+    const V* v0 = val + g * D * 64 + lane;
+    const int p = id[i];
+    // short chains of additions: FP32 errors (norms, against 64 bits) of the
+    // 27- and 7-point products 5.2e-8 and 4.6e-8 with these, 5.7e-8 and 4.6e-8
+    // in the rows-from-LDS kernel
+    constexpr int A = S == 9 ? 5 : 4;
+    T a[A];
+#pragma unroll
+    for (int u = 0; u < A; ++u) a[u] = T(0);
+    uint64_t m = 0;
+    // every shift of the slice lies inside x, or (the first and last slices)
+    // is moved inside where it does not: those values are not used
+    const auto body = [&](auto at) {
+      for (int j = 0; j < D; j += S) {
+        typename Raw<V>::type v[S];
+#pragma unroll
+        for (int u = 0; u < S; ++u)
+          if (FULL || j + u < D) {
+            if constexpr (NT)
+              v[u] = ld_stream<true>(v0 + (j + u) * 64);
+            else
+              v[u] = Raw<V>::load(v0, (j + u) * 64);
+          }
+        T q[S];
+        if constexpr (TRI) {
+          T e[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            if (FULL || j + 3 * u < D) q[3 * u + 1] = at(i + off[j + 3 * u + 1]);
+          if (lane == 0 || lane == 63) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+              if (FULL || j + 3 * u < D)
+                e[u] = at(i + off[j + 3 * u + 1] + (lane == 0 ? -1 : 1));
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            q[3 * u] = lane_shift<true>(q[3 * u + 1], e[u]);
+            q[3 * u + 2] = lane_shift<false>(q[3 * u + 1], e[u]);
+          }
+        } else {
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            if (FULL || j + u < D) q[u] = at(i + off[j + u]);
+        }
+        if (j == 0) m = mask[p];
+        const uint32_t mm = (uint32_t)(m >> j);
+#pragma unroll
+        for (int u = 0; u < S; ++u)
+          if (FULL || j + u < D)
+            a[u % A] += (mm >> u) & 1 ? to_acc(Raw<V>::value(v[u])) * q[u] : T(0);
+      }
+    };
+    if (g * 64 + lo >= 0 && g * 64 + 63 + hi < ncols)
+      body([&](int64_t c) { return x[c]; });
+    else
+      body([&](int64_t c) { return x[c < 0 ? 0 : c < ncols ? c : ncols - 1]; });
+    if (i < n) {
+#pragma unroll
+      for (int h = 1; h < A; h *= 2)  // pairs, then pairs of these
+#pragma unroll
+        for (int u = 0; u + h < A; u += 2 * h) a[u] += a[u + h];
+      T acc = a[0];
+      if (SCALED) acc *= (T)scale[i];
+      const T out = combine(alpha, acc, beta, y, i);
+      y[i] = out;
+      if constexpr (NV > 0) d0 += (double)w[i] * (double)out;
+      if constexpr (NV > 1) d1 += (double)out * (double)out;
+    }
+  }
+  if constexpr (NV > 0) {
+    __shared__ double red[2][4];
+    d0 = wave_total(d0);
+    if constexpr (NV > 1) d1 = wave_total(d1);
+    if (lane == 0) {
+      red[0][wv] = d0;
+      red[1][wv] = d1;
+    }
+    __syncthreads();
+    if (threadIdx.x < NV) {
+      const double* r = red[threadIdx.x];
+      part[(int64_t)blockIdx.x * NV + threadIdx.x] = ((r[0] + r[1]) + r[2]) + r[3];
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
+// Value types that are kept by diagonals.
+template <typename V>
+constexpr bool kDiagValue = std::is_same_v<V, double> || std::is_same_v<V, float> ||
+                            std::is_same_v<V, _Float16>;
+
+// nv > 0: at most kDotPartials work-groups, whose number is returned
+template <typename V, typename T, bool SCALED>
+int launch_diag(mxs_ctx* ctx, const mxs_matrix* A, const DiagPart& P, const float* scale, T alpha,
+                const T* x, T beta, T* y, const int32_t* skip, const T* w = nullptr,
+                double* part = nullptr, int nv = 0) {
+  const int64_t groups = (A->n + 255) / 256;
+  const int R = nv ? (int)((groups + kDotPartials - 1) / kDotPartials) : 1;
+  const int g = (int)((groups + R - 1) / R);
+  const auto go = [&](auto nvc, auto nt, auto u, auto tri, auto full) {
+    k_diag<V, T, SCALED, decltype(nvc)::value, decltype(nt)::value, decltype(u)::value,
+           decltype(tri)::value, decltype(full)::value><<<g, 256, 0, ctx->stream>>>(
+        A->n, A->ncols, R, P.D, P.lo, P.hi, scale, P.off, P.id, P.mask, (const V*)P.val, x, y,
+        alpha, beta, skip, w, part);
+  };
+  using std::integral_constant;
+  // whole rounds of 9, 7 or 5 diagonals where D allows (27, 7 and 5 points),
+  // else rounds of 8 with a last one that is not full
+  const auto shape = [&](auto nvc, auto nt) {
+    const std::true_type yes;
+    const std::false_type no;
+    if (P.threes && P.D % 9 == 0)
+      go(nvc, nt, integral_constant<int, 3>(), yes, yes);
+    else if (P.threes)
+      go(nvc, nt, integral_constant<int, 3>(), yes, no);
+    else if (P.D % 9 == 0)
+      go(nvc, nt, integral_constant<int, 9>(), no, yes);
+    else if (P.D % 7 == 0)
+      go(nvc, nt, integral_constant<int, 7>(), no, yes);
+    else if (P.D % 5 == 0)
+      go(nvc, nt, integral_constant<int, 5>(), no, yes);
+    else
+      go(nvc, nt, integral_constant<int, 8>(), no, no);
+  };
+  if (nv == 2)
+    shape(integral_constant<int, 2>(), std::false_type());
+  else if (nv == 1)
+    shape(integral_constant<int, 1>(), std::false_type());
+  else if (kNtValue<V> && (double)P.D * A->n * sizeof(V) > kStreamNtBytes)
+    shape(integral_constant<int, 0>(), integral_constant<bool, kNtValue<V>>());
+  else
+    shape(integral_constant<int, 0>(), std::false_type());
+  return g;
+}
+
 template <typename V, typename T, int G, bool SCALED>
 void launch_csr_vec(mxs_ctx* ctx, const mxs_matrix* A, T alpha, const T* x, T beta, T* y,
                     const int32_t* skip) {
@@ -1585,6 +1780,12 @@ void launch_csr(mxs_ctx* ctx, const mxs_matrix* A, T alpha, const T* x, T beta, 
       launch_csr_merge<V, T, SCALED>(ctx, A, alpha, x, beta, y, skip, scratch);
     return;
   }
+  if constexpr (kDiagValue<V>) {
+    if (P.diag.on()) {
+      launch_diag<V, T, SCALED>(ctx, A, P.diag, P.scale, alpha, x, beta, y, skip);
+      return;
+    }
+  }
   // col and val of a matrix larger than the Infinity Cache are streamed
   // non-temporally
   const bool nt = (double)A->nnz * (4 + sizeof(V)) > kStreamNtBytes;
@@ -1752,6 +1953,13 @@ void launch_ell(mxs_ctx* ctx, const mxs_matrix* A, T alpha, const T* x, T beta, 
 template <typename V, typename T, bool SCALED>
 void launch_typed(mxs_ctx* ctx, const mxs_matrix* A, T alpha, const T* x, T beta, T* y,
                   const int32_t* skip, void* scratch, size_t bytes) {
+  if constexpr (!SCALED) {
+    const DiagPart& D = A->fmt == MXS_COO ? A->coo.diag : A->ell.diag;
+    if (A->fmt != MXS_CSR && D.on()) {
+      launch_diag<V, T, false>(ctx, A, D, nullptr, alpha, x, beta, y, skip);
+      return;
+    }
+  }
   switch (A->fmt) {
     case MXS_CSR:
       launch_csr<V, T, SCALED>(ctx, A, alpha, x, beta, y, skip, scratch, bytes);
@@ -1885,6 +2093,9 @@ int launch_dot_typed(mxs_ctx* ctx, const mxs_matrix* A, const T* x, T* y, const 
                                  skip, scratch, ctx->spmv_ws.bytes, dpart, w ? w : x, nv);
     return (int)P.bin.nbins;
   }
+  if (P.diag.on())
+    return launch_diag<V, T, SCALED>(ctx, A, P.diag, P.scale, T(1), x, T(0), y, skip, w ? w : x,
+                                     dpart, nv);
   if (P.rows_lds && P.nblocks > 0) {
     const T* wd = w ? w : x;
     if (P.block_nnz <= 512)
@@ -1910,8 +2121,8 @@ int launch_spmv_dot(mxs_ctx* ctx, const mxs_matrix* A, const void* x, void* y,
                     const int32_t* skip, double* dpart, const void* w, int nv) {
   if (A->fmt != MXS_CSR || A->n == 0 || A->n != A->ncols || nv < 1 || nv > 2) return 0;
   const CsrPart& P = A->csr;
-  if (!(P.rows_lds && P.nblocks > 0) && !(P.merge && P.nchunks > 0)) return 0;
-  if (!P.bin.on() && !(P.rows_lds && P.nblocks > 0) && ((w && w != x) || nv != 1)) return 0;
+  if (!P.diag.on() && !(P.rows_lds && P.nblocks > 0) && !(P.merge && P.nchunks > 0)) return 0;
+  if (!P.bin.on() && !P.diag.on() && !(P.rows_lds && P.nblocks > 0) && ((w && w != x) || nv != 1)) return 0;
   // the merge path without panels also keeps one dot partial per chunk
   const size_t need = spmv_scratch_bytes(A) +
                       (P.merge && P.panels <= 1 && !P.bin.on() ? (size_t)P.nchunks * sizeof(double) : 0);

@@ -97,7 +97,7 @@ def traffic(fetch_csv: str, write_csv: str, out: str, command: str,
              "# kernel grid fetch_kib write_kib scaled_bytes"]
     for k in sorted(fe):
         name, grid = k
-        if not name.startswith(("k_csr", "k_coo", "k_ell", "k_panel", "k_cg", "k_probe")):
+        if not name.startswith(("k_csr", "k_diag", "k_bin", "k_coo", "k_ell", "k_panel", "k_cg", "k_probe")):
             continue
         f_ = fe[k]
         w_ = wr.get(k, 0.0)
