@@ -621,6 +621,21 @@ __device__ __forceinline__ void cg_body(const SlotDesc& D, SlotState* S, int K, 
   }
 }
 
+// The longest row with which a work-group of bs threads and rpt rows a thread
+// keeps its matrix in registers (0: never).  What bounds a work-group's
+// iteration is its instruction issue and its barriers, so fewer threads with
+// more registers each do it faster: at 4096 rows of 5, 512 threads (256
+// registers a lane, 40 entries) take 2.06 us an iteration, 1024 (128
+// registers, 20 entries) 2.84, and a matrix streamed from the L2 12.  Where a
+// form needs more registers than a lane has, it streams.
+constexpr int reg_row(int bs, int rpt, bool lds) {
+  return !lds                    ? 0
+         : rpt <= 4              ? (bs == 1024 ? 20 : 24) / rpt
+         : bs <= 512 && rpt <= 8 ? 40 / rpt
+         : bs <= 256 && rpt <= 10 ? 5
+                                 : 0;
+}
+
 template <int BS, int RPT, bool USE_LDS, int MODE>
 __global__ __launch_bounds__(BS) void k_batch_cg(const SlotDesc* __restrict__ desc,
                                                  SlotState* __restrict__ state, int base, int K,
@@ -682,16 +697,19 @@ __global__ __launch_bounds__(BS) void k_batch_cg(const SlotDesc* __restrict__ de
     ir_body<BS, RPT, USE_LDS>(D, S, K, fresh, rpl, maxlen, dyn, red);
     return;
   }
-  // matrices small enough for registers (at most 24 entries a thread, 20 at
-  // 1024 threads, whose lanes have 128 registers; a row's entries at most
-  // that / RPT) are loaded once per launch and every product of the launch
-  // reads them there; the rest stream theirs
-  constexpr int ML = USE_LDS && RPT <= 4 ? (BS == 1024 ? 20 : 24) / RPT : 0;
+  // a matrix whose rows have at most reg_row() entries is loaded into
+  // registers once per launch and every product of the launch reads it there;
+  // the others stream theirs
+  constexpr int ML = reg_row(BS, RPT, USE_LDS);
   if constexpr (ML > 0) {
     if (maxlen <= ML) {
-      int32_t cr[RPT * ML];
+      // columns as byte offsets into the gather vector, two a register (at
+      // most 4096 rows of 8 bytes); a slot past its row's end holds 0 and the
+      // row's first column, so the products need no test per entry
+      constexpr int NC = (RPT * ML + 1) / 2;
+      static_assert(BS * RPT * sizeof(double) <= 65536, "16-bit offsets");
+      uint32_t cr[NC] = {};
       double vr[RPT * ML];
-      uint32_t hm = 0;
 #pragma unroll
       for (int k = 0; k < RPT; ++k) {
         const int i = tid + k * BS;
@@ -699,20 +717,31 @@ __global__ __launch_bounds__(BS) void k_batch_cg(const SlotDesc* __restrict__ de
 #pragma unroll
         for (int j = 0; j < ML; ++j) {
           const bool h = a + j < e;
-          const int32_t es = h ? a + j : 0;
-          cr[k * ML + j] = col[es];
-          vr[k * ML + j] = val[es];
-          hm |= (h ? 1u : 0u) << (k * ML + j);
+          const int32_t es = h ? a + j : a < e ? a : 0;
+          const uint32_t c = a < e ? (uint32_t)col[es] * 8u : 0u;
+          const double v = val[es];
+          vr[k * ML + j] = h ? v : 0.0;
+          cr[(k * ML + j) / 2] |= c << (16 * ((k * ML + j) & 1));
         }
       }
-      auto spmv_reg = [&](const double* __restrict__ v, double (&q)[RPT]) {
+      // (explicit LDS addresses: from an offset into a generic pointer the
+      // compiler would make flat loads)
+      typedef __attribute__((address_space(3))) const double lds_double;
+      const uint32_t base =
+          (uint32_t)(uintptr_t)(__attribute__((address_space(3))) double*)dyn;
+      auto spmv_reg = [&](const double* __restrict__, double (&q)[RPT]) {
+        // (unpacked anew by every product, instead of once before the loop
+        // into twice the registers)
+#pragma unroll
+        for (int t = 0; t < NC; ++t) asm volatile("" : "+v"(cr[t]));
 #pragma unroll
         for (int k = 0; k < RPT; ++k) {
           double acc = 0.0;
 #pragma unroll
           for (int j = 0; j < ML; ++j) {
-            const double g = v[cr[k * ML + j]];
-            if ((hm >> (k * ML + j)) & 1u) acc += vr[k * ML + j] * g;
+            const int t = k * ML + j;
+            const uint32_t c = t & 1 ? cr[t / 2] >> 16 : cr[t / 2] & 0xFFFFu;
+            acc += vr[t] * *(lds_double*)(uintptr_t)(base + c);
           }
           q[k] = acc;
         }
@@ -1103,15 +1132,13 @@ mxs_status upload_desc(mxs_batch* B) {
 // ---------------------------------------------------------------------------
 // one system through the batched kernel (the single-system solver's path for
 // small matrices): a one-slot descriptor in device scratch, one work-group
-// of 1024 threads, up to 1024 iterations per launch
+// of 256 to 1024 threads, up to 1024 iterations per launch
 // ---------------------------------------------------------------------------
-constexpr int kSmallBlock = 1024;
-
 bool small_cg_fits(int64_t n, int64_t max_row) { return n >= 1 && n <= 8192 && max_row <= 64; }
 
 size_t small_cg_scratch(int64_t n) { return 2 * kAlign + 2 * up((size_t)n * sizeof(double)); }
 
-mxs_status small_cg(mxs_ctx* ctx, const mxs_matrix* A, const double* b, double* x,
+mxs_status small_cg(mxs_ctx* ctx, const mxs_matrix* A, int64_t max_row, const double* b, double* x,
                     double rel_tol, double abs_tol, bool base_r0, int64_t max_iters,
                     void* scratch, void* pinned, SmallCgResult* res) {
   static_assert(sizeof(SlotDesc) <= kAlign && sizeof(SlotState) <= kAlign, "staging layout");
@@ -1146,7 +1173,17 @@ mxs_status small_cg(mxs_ctx* ctx, const mxs_matrix* A, const double* b, double* 
   hd.gen = 1;  // the zeroed state's gen differs: the first launch starts fresh
   ClassCfg C{};
   C.max_n = (int)n;
-  C.block = kSmallBlock;
+  // the fewest threads that keep the matrix in registers at no more than 4
+  // (256 threads) or 8 rows a thread: 1024 rows of 5 take 146 us a solve with
+  // 256 threads, 163 with 512, 240 with 1024; 2025 rows 192 with 512, 198
+  // with 256, 278 with 1024; 4096 rows 256 with 512, 390 with 1024.  A matrix
+  // that neither holds is left to all the wavefronts a work-group can have.
+  C.block = 1024;
+  for (const auto& f : {std::pair<int, int>{256, 4}, {512, 8}})
+    if (n <= f.first * f.second && max_row <= reg_row(f.first, rpt_for((int)n, f.first), true)) {
+      C.block = f.first;
+      break;
+    }
   C.rpt = rpt_for(C.max_n, C.block);
   C.lds = true;
   const size_t lds = class_lds(C);

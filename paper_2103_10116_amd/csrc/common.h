@@ -327,8 +327,8 @@ constexpr size_t kSmallCgPinned = 768;  // pinned staging bytes small_cg needs
 // FP64 CG on one small CSR system in one work-group, from x0 = x (updated in
 // place): r0 = b - A x0, the threshold max(rel_tol * base, abs_tol) with
 // base = ||r0|| (base_r0) or ||b||, every iteration and the true-residual
-// check run in the kernel; b = 0 gives x = 0.
-mxs_status small_cg(mxs_ctx* ctx, const mxs_matrix* A, const double* b, double* x,
+// check run in the kernel; b = 0 gives x = 0.  max_row: the longest row.
+mxs_status small_cg(mxs_ctx* ctx, const mxs_matrix* A, int64_t max_row, const double* b, double* x,
                     double rel_tol, double abs_tol, bool base_r0, int64_t max_iters,
                     void* scratch, void* pinned, SmallCgResult* res);
 

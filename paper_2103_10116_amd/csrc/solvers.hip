@@ -1506,25 +1506,26 @@ mxs_status zero_solution(mxs_ctx* ctx, double* x, int64_t n, mxs_solve_info* inf
   return MXS_OK;
 }
 
-bool small_path(const mxs_matrix* A, const Stop& stop) {
+bool small_path(const mxs_matrix* A, const Stop& stop, int64_t* max_row) {
   if (A->fmt != MXS_CSR || A->dt != MXS_F64 || stop.max_repl != 3 || A->n > 8192) return false;
   int64_t maxL = 0;
   for (int64_t i = 0; i < A->n; ++i)
     maxL = std::max<int64_t>(maxL, A->h_rowptr[i + 1] - A->h_rowptr[i]);
+  *max_row = maxL;
   return small_cg_fits(A->n, maxL);
 }
 
 // CG on a small CSR system: one work-group runs the whole solve (initial
 // residual, norms, iterations, true-residual check) and x is updated in
 // place; the host only reads the final state.
-mxs_status solve_cg_small(mxs_ctx* ctx, const mxs_matrix* A, const double* b, double* x,
-                          const Stop& stop, mxs_solve_info* info) {
+mxs_status solve_cg_small(mxs_ctx* ctx, const mxs_matrix* A, int64_t max_row, const double* b,
+                          double* x, const Stop& stop, mxs_solve_info* info) {
   const int64_t n = A->n;
   if (!ws_reserve(ctx, small_cg_scratch(n)))
     return fail(ctx, MXS_OOM, "solver workspace of %zu bytes", small_cg_scratch(n));
   if (!pinned_reserve(ctx, kSmallCgPinned)) return fail(ctx, MXS_OOM, "pinned staging");
   SmallCgResult sr;
-  mxs_status s = small_cg(ctx, A, b, x, stop.rel_tol, stop.abs_tol,
+  mxs_status s = small_cg(ctx, A, max_row, b, x, stop.rel_tol, stop.abs_tol,
                           stop.baseline == MXS_BASELINE_INITIAL, stop.max_iters, ctx->ws.ptr,
                           ctx->pinned, &sr);
   if (s) return s;
@@ -1560,7 +1561,8 @@ mxs_status solve_cg_small(mxs_ctx* ctx, const mxs_matrix* A, const double* b, do
 
 mxs_status solve_cg(mxs_ctx* ctx, const mxs_matrix* A, const double* b, double* x,
                     const Stop& stop, mxs_solve_info* info) {
-  if (small_path(A, stop)) return solve_cg_small(ctx, A, b, x, stop, info);
+  int64_t max_row;
+  if (small_path(A, stop, &max_row)) return solve_cg_small(ctx, A, max_row, b, x, stop, info);
   const int64_t n = A->n;
   const size_t ld = align_up((size_t)n, 64);
   Work w;
