@@ -60,9 +60,6 @@ struct mxs_ctx {
   // cache-flush buffer
   void* flush = nullptr;
   size_t flush_bytes = 0;
-  // solver status polling: two copies of the device state in flight, each
-  // marked by an event (created with the ctx)
-  hipEvent_t poll_ev[2] = {nullptr, nullptr};
 };
 
 namespace mxs {

@@ -13,8 +13,9 @@
 //    finishing kernel) add them in block order, so an iteration never waits
 //    for the host and needs no device-scope fence;
 //  * a device status word stops all queued work once the solver converged
-//    or broke down: the host enqueues `check_every` iterations, then reads
-//    the status once (pinned memory);
+//    or broke down: the kernel that decides it also writes it, with the
+//    iteration count, to a word of pinned host memory, and the host keeps a
+//    few iterations queued beyond the count that it reads there;
 //  * reductions accumulate in FP64 (also for the FP32 inner solver of
 //    iterative refinement) with a fixed order: per-thread grid-stride sums,
 //    wave butterflies, wave partials in order, block partials in order.
@@ -22,6 +23,7 @@
 #include <cmath>
 #include <cstring>
 #include <new>
+#include <thread>
 
 #include "common.h"
 
@@ -67,7 +69,30 @@ struct KState {
   // the kernel that decides it, so that the other blocks of that same
   // launch, which may already see `done`, still finish their x update
   int64_t halt;
+  // the host's word (run_polled): iterations << 8 | terminal status, with
+  // MAIL_CYCLE once a GMRES cycle must end
+  uint64_t* mail;
 };
+
+constexpr int32_t MAIL_CYCLE = 0x80;
+
+// By the lead thread, when it has decided.  The wavefront's next wait for a
+// load waits for this store to reach the host as well, 1 to 2 us that the
+// kernel's last block then ends later: a count is sent every kPostEvery
+// iterations (CG on the 7-point grid 128^3: 7.37 ms with no store, 7.58 with
+// one an iteration, 7.31 so).
+constexpr int64_t kPostEvery = 4;
+
+__device__ __forceinline__ void post(KState* st, int64_t iters, int32_t done) {
+  if (st->mail && (done != RUN || iters % kPostEvery == 0))
+    __hip_atomic_store(st->mail, (uint64_t)iters << 8 | (uint64_t)done, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+__device__ __forceinline__ void stop_with(KState* st, int32_t verdict) {
+  st->done = verdict;
+  post(st, st->iters, verdict);
+}
 
 int red_grid(int64_t n) {
   int64_t g = (n + RB * 4 - 1) / (RB * 4);
@@ -373,8 +398,10 @@ __global__ __launch_bounds__(RB) void k_cg_r(int64_t n, T* __restrict__ r,
         broke = !isfinite(pq[0]) || pq[0] <= 0.0;
         if (broke) {
           if (lead()) {
-            st->done = isfinite(pq[0]) ? ST_BREAKDOWN : ST_NONFINITE;
+            const int32_t verdict = isfinite(pq[0]) ? ST_BREAKDOWN : ST_NONFINITE;
+            st->done = verdict;
             st->halt = k + 1;
+            post(st, k, verdict);
           }
           return;
         }
@@ -410,13 +437,12 @@ __global__ __launch_bounds__(RB) void k_cg_xp(int64_t n, T* __restrict__ x,
     st->iters = k + 1;
     st->res2 = rn;
     st->rho[1 - par] = rn;
-    if (bad)
-      st->done = ST_NONFINITE;
-    else if (conv)
-      st->done = ST_CONVERGED;
-    else if (maxit)
-      st->done = ST_MAXIT;
-    if (stop) st->halt = k + 2;
+    const int32_t verdict = bad ? ST_NONFINITE : conv ? ST_CONVERGED : maxit ? ST_MAXIT : RUN;
+    if (stop) {
+      st->done = verdict;
+      st->halt = k + 2;
+    }
+    post(st, k + 1, verdict);
   }
   const T a = (T)st->alpha;
   if (stop) {
@@ -472,7 +498,10 @@ __global__ __launch_bounds__(RB) void k_bi_p(int64_t n, const double* __restrict
   if (lead()) {
     st->res2 = rn;
     st->rho[1 - par] = rhr;
-    if (verdict != RUN) st->done = verdict;
+    if (verdict != RUN) {
+      st->done = verdict;
+      post(st, k, verdict);
+    }
   }
   if (verdict != RUN) return;
   const double beta = (rhr / st->rho[par]) * (a / w);
@@ -501,7 +530,7 @@ __global__ __launch_bounds__(RB) void k_bi_s(int64_t n, const double* __restrict
   double rv[1];
   finish_wide<1>(pa, g, rv);  // the product's partials when it formed r_hat.v
   if (!isfinite(rv[0]) || rv[0] == 0.0) {
-    if (lead()) st->done = isfinite(rv[0]) ? ST_BREAKDOWN : ST_NONFINITE;
+    if (lead()) stop_with(st, isfinite(rv[0]) ? ST_BREAKDOWN : ST_NONFINITE);
     return;
   }
   const double a = st->rho[1 - par] / rv[0];
@@ -525,14 +554,14 @@ __global__ __launch_bounds__(RB) void k_bi_omega(int64_t n, const double* __rest
   double ss[1];
   finish<1>(pb, g, ss);
   if (!isfinite(ss[0])) {
-    if (lead()) st->done = ST_NONFINITE;
+    if (lead()) stop_with(st, ST_NONFINITE);
     return;
   }
   if (sqrt(ss[0]) <= st->thr) {
     if (lead()) {
       st->res2 = ss[0];
       st->iters = k + 1;
-      st->done = ST_HALF;
+      stop_with(st, ST_HALF);
     }
     return;
   }
@@ -564,14 +593,14 @@ __global__ __launch_bounds__(RB) void k_bi_update(int64_t n, double* __restrict_
     double ss[1];
     finish<1>(pb, gb, ss);
     if (!isfinite(ss[0])) {
-      if (lead()) st->done = ST_NONFINITE;
+      if (lead()) stop_with(st, ST_NONFINITE);
       return;
     }
     if (sqrt(ss[0]) <= st->thr) {
       if (lead()) {
         st->res2 = ss[0];
         st->iters = k + 1;
-        st->done = ST_HALF;
+        stop_with(st, ST_HALF);
       }
       return;
     }
@@ -579,7 +608,7 @@ __global__ __launch_bounds__(RB) void k_bi_update(int64_t n, double* __restrict_
   double tstt[2];
   finish_wide<2>(pd, g, tstt);
   if (!isfinite(tstt[0]) || !isfinite(tstt[1]) || tstt[1] == 0.0) {
-    if (lead()) st->done = tstt[1] == 0.0 ? ST_BREAKDOWN : ST_NONFINITE;
+    if (lead()) stop_with(st, tstt[1] == 0.0 ? ST_BREAKDOWN : ST_NONFINITE);
     return;
   }
   const double w = tstt[0] / tstt[1];
@@ -587,6 +616,7 @@ __global__ __launch_bounds__(RB) void k_bi_update(int64_t n, double* __restrict_
   if (lead()) {
     st->omega = w;
     st->iters = k + 1;
+    post(st, k + 1, RUN);
   }
   double acc[2] = {0.0, 0.0};
   strided4(
@@ -772,9 +802,11 @@ __global__ __launch_bounds__(RB) void k_gm_fin(const double* __restrict__ part, 
   if (verdict == 0 && t <= j + 1) Hj[t] = hc[t];
 }
 
-// v_{j+1} = w / h_{j+1,j}
+// v_{j+1} = w / h_{j+1,j}.  Reports what k_gm_fin has decided: that one-block
+// kernel would end only when the store has reached the host (2 us).
 __global__ __launch_bounds__(RB) void k_gm_scale(int64_t n, const double* __restrict__ w,
-                                                 double* __restrict__ vn, const KState* st) {
+                                                 double* __restrict__ vn, KState* st) {
+  if (lead()) post(st, st->iters, st->done | (st->cycle ? MAIL_CYCLE : 0));
   if (st->done || st->cycle) return;
   const double inv = 1.0 / st->res2;
   strided4(
@@ -926,6 +958,7 @@ __global__ __launch_bounds__(RB) void k_pipe_update(int64_t n, double* __restric
   if (lead()) {
     st->res2 = gamma;
     st->iters = verdict == RUN ? k + 1 : k;
+    post(st, st->iters, verdict);
     if (verdict != RUN) {
       st->done = verdict;
     } else {
@@ -995,7 +1028,7 @@ __global__ __launch_bounds__(RB) void k_cgs_qw(int64_t n, const double* __restri
   double sg[1];
   finish_wide<1>(pa, g, sg);  // the product's partials when it formed r_hat.v
   if (!isfinite(sg[0]) || sg[0] == 0.0) {
-    if (lead()) st->done = isfinite(sg[0]) ? ST_BREAKDOWN : ST_NONFINITE;
+    if (lead()) stop_with(st, isfinite(sg[0]) ? ST_BREAKDOWN : ST_NONFINITE);
     return;
   }
   const double a = st->rho[par] / sg[0];
@@ -1054,6 +1087,7 @@ __global__ __launch_bounds__(RB) void k_cgs_dir(int64_t n, const double* __restr
     st->res2 = rr;
     st->rho[1 - par] = rhr;
     if (verdict != RUN) st->done = verdict;
+    post(st, k + 1, verdict);
   }
   if (verdict != RUN) return;
   const double beta = rhr / st->rho[par];
@@ -1132,7 +1166,7 @@ __global__ __launch_bounds__(RB) void k_pcg_update(int64_t n, T* __restrict__ x,
   double pq[1];
   finish<1>(pa, g, pq);
   if (!isfinite(pq[0]) || pq[0] <= 0.0) {
-    if (lead()) st->done = isfinite(pq[0]) ? ST_BREAKDOWN : ST_NONFINITE;
+    if (lead()) stop_with(st, isfinite(pq[0]) ? ST_BREAKDOWN : ST_NONFINITE);
     return;
   }
   const double alpha = st->rho[par] / pq[0];
@@ -1191,14 +1225,13 @@ __global__ __launch_bounds__(RB) void k_pcg_direction(int64_t n, const T* __rest
     st->iters = k + 1;
     st->res2 = rr;
     st->rho[1 - par] = rz;
-    if (bad)
-      st->done = ST_NONFINITE;
-    else if (conv)
-      st->done = ST_CONVERGED;
-    else if (maxit)
-      st->done = ST_MAXIT;
-    else if (brk)
-      st->done = ST_BREAKDOWN;
+    const int32_t verdict = bad     ? ST_NONFINITE
+                            : conv  ? ST_CONVERGED
+                            : maxit ? ST_MAXIT
+                            : brk   ? ST_BREAKDOWN
+                                    : RUN;
+    if (verdict != RUN) st->done = verdict;
+    post(st, k + 1, verdict);
   }
   if (bad || conv || maxit || brk) return;
   const T beta = (T)(rz / st->rho[par]);
@@ -1277,6 +1310,7 @@ __global__ __launch_bounds__(RB) void k_pr_update(int64_t n, double* __restrict_
     if (k > 0) st->res2 = change;
     st->iters = verdict == RUN ? k + 1 : k;  // steps taken once this one is done
     if (verdict != RUN) st->done = verdict;
+    post(st, st->iters, verdict);
   }
   if (verdict != RUN) return;
   const double nd = (double)n;
@@ -1307,6 +1341,7 @@ struct Work {
   double* pm;        // MAXG * MAXM doubles (GMRES multi-dots)
   double* pw;        // kDotPartials doubles (partials of a product with its dot)
   char* vec;         // vectors
+  uint64_t* mail;    // pinned: see KState::mail
 };
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -1318,8 +1353,8 @@ mxs_status get_work(mxs_ctx* ctx, size_t vec_bytes, Work* w) {
   const size_t pw = (size_t)kDotPartials * sizeof(double);
   const size_t total = st_bytes + 4 * p2 + pm + pw + vec_bytes + 256;
   if (!ws_reserve(ctx, total)) return fail(ctx, MXS_OOM, "solver workspace of %zu bytes", total);
-  // host mirror + the two polling copies
-  if (!pinned_reserve(ctx, 3 * st_bytes)) return fail(ctx, MXS_OOM, "pinned state mirror");
+  // host mirror + the word that the kernels report to
+  if (!pinned_reserve(ctx, st_bytes + 256)) return fail(ctx, MXS_OOM, "pinned state mirror");
   char* base = (char*)ctx->ws.ptr;
   w->st = (KState*)base;
   w->pa = (double*)(base + st_bytes);
@@ -1330,11 +1365,13 @@ mxs_status get_work(mxs_ctx* ctx, size_t vec_bytes, Work* w) {
   w->pw = (double*)(base + st_bytes + 4 * p2 + pm);
   w->vec = base + st_bytes + 4 * p2 + pm + pw;
   w->hst = (KState*)ctx->pinned;
+  w->mail = (uint64_t*)((char*)ctx->pinned + st_bytes);
   MXS_HIP_TRY(ctx, hipMemsetAsync(w->st, 0, sizeof(KState), ctx->stream));
   return MXS_OK;
 }
 
 mxs_status push_state(mxs_ctx* ctx, Work& w) {
+  w.hst->mail = w.mail;
   MXS_HIP_TRY(ctx, hipMemcpyAsync(w.st, w.hst, sizeof(KState), hipMemcpyHostToDevice,
                                   ctx->stream));
   // the pinned buffer is reused by pull_state: the upload must finish first
@@ -1410,78 +1447,89 @@ Stop read_stop(const mxs_stop* s, int64_t default_max) {
   return o;
 }
 
-// Runs CG iterations from the state already on the device until the
-// device status is set.  Vectors of type T; the operator is A.
-// The host polls the device status without leaving the GPU idle: after
-// each batch of `check_every` iterations it enqueues a copy of the state
-// into one of two pinned slots and an event, enqueues the next batch, and
-// only then waits for the previous batch's copy.  A batch enqueued after
-// the one that finished the solve returns at once in every kernel.
-struct StatusPoll {
-  mxs_ctx* ctx;
-  Work& w;
-  KState* slot[2];
-  StatusPoll(mxs_ctx* c, Work& wk) : ctx(c), w(wk) {
-    const size_t stb = align_up(sizeof(KState), 256);
-    slot[0] = (KState*)((char*)ctx->pinned + stb);
-    slot[1] = (KState*)((char*)ctx->pinned + 2 * stb);
-  }
-  mxs_status record(int s) {
-    MXS_HIP_TRY(ctx, hipMemcpyAsync(slot[s], w.st, sizeof(KState), hipMemcpyDeviceToHost,
-                                    ctx->stream));
-    MXS_HIP_TRY(ctx, hipEventRecord(ctx->poll_ev[s], ctx->stream));
-    return MXS_OK;
-  }
-  mxs_status wait(int s) {
-    MXS_HIP_TRY(ctx, hipEventSynchronize(ctx->poll_ev[s]));
-    return MXS_OK;
-  }
-};
-
-// Enqueues batch(k0) for k0 = k, k + C, k + 2C, ... until the device status
-// is set, polling it through StatusPoll; returns with the final state in
-// w.hst.
-template <typename Batch>
-mxs_status run_polled(mxs_ctx* ctx, Work& w, int64_t k, int C, const char* what, Batch batch) {
-  StatusPoll poll(ctx, w);
-  mxs_status s;
-  if ((s = batch(k)) || (s = poll.record(0))) return s;
-  int cur = 0;
-  int64_t seen = k;
-  for (int64_t kq = k + C;; kq += C) {
-    if ((s = batch(kq)) || (s = poll.record(1 - cur)) || (s = poll.wait(cur))) return s;
-    const KState& sn = *poll.slot[cur];
-    if (sn.done) return pull_state(ctx, w);
-    if (sn.iters <= seen)
+// Reads the word that the kernels report to until the count has reached
+// `target` (the last count up to it that they send) or the solve (or GMRES cycle) has ended (*ended).  A stream that
+// has nothing left to run by then is read itself: a solve cannot hang here.
+mxs_status await_iters(mxs_ctx* ctx, Work& w, int64_t target, int64_t* seen, bool* ended,
+                       const char* what) {
+  target -= target > 0 ? target % kPostEvery : 0;
+  for (unsigned spin = 1;; ++spin) {
+    const uint64_t v = __atomic_load_n(w.mail, __ATOMIC_ACQUIRE);
+    *ended = (v & 0xFF) != 0;
+    *seen = (int64_t)(v >> 8);
+    if (*ended || *seen >= target) return MXS_OK;
+    if (spin % 1024 == 0) {
+      const hipError_t e = hipStreamQuery(ctx->stream);
+      if (e == hipErrorNotReady) {
+        (void)hipGetLastError();
+        std::this_thread::yield();
+        continue;
+      }
+      MXS_HIP_TRY(ctx, e);
+      mxs_status s = pull_state(ctx, w);
+      if (s) return s;
+      *ended = w.hst->done != RUN || w.hst->cycle != 0;
+      *seen = w.hst->iters;
+      if (*ended || *seen >= target) return MXS_OK;
       return fail(ctx, MXS_HIP, "%s made no progress (device state not updated)", what);
-    seen = sn.iters;
-    cur = 1 - cur;
+    }
+    __builtin_ia32_pause();
   }
 }
 
+// Enqueues iteration(k0), iteration(k0 + 1), ... until the device status is
+// set, staying at most min(C, kAhead) iterations ahead of the last count that
+// the kernels have sent; returns with the final state in w.hst.  The
+// iterations queued beyond the last one return at once in every kernel, but
+// each of their launches still takes 2 to 3 us.  With 16 to 32 of them and a
+// copy of the state every 16 iterations, as a host that waits for copies
+// needs, 21 iterations of Jacobi CG on 2^18 rows take 1.11 ms, with at most 7
+// and no copies 0.95; 150 of CG on the 7-point grid 40^3 2.08 and 1.84;
+// refinement on 120^3, 5 inner solves, 5.98 and 5.70.
+constexpr int64_t kAhead = 4;
+
+void mail_reset(Work& w, int64_t k) {
+  __atomic_store_n(w.mail, (uint64_t)k << 8, __ATOMIC_RELEASE);
+}
+
+template <typename Iteration>
+mxs_status run_polled(mxs_ctx* ctx, Work& w, int64_t k0, int C, const char* what,
+                      Iteration iteration) {
+  const int64_t ahead = std::min<int64_t>(C, kAhead);
+  mail_reset(w, k0);
+  bool ended = false;
+  int64_t seen = k0;
+  mxs_status s;
+  for (int64_t k = k0; !ended; ++k) {
+    if ((s = iteration(k))) return s;
+    if ((s = await_iters(ctx, w, k + 1 - ahead, &seen, &ended, what))) return s;
+  }
+  return pull_state(ctx, w);
+}
+
+// Runs CG iterations from the state already on the device until the
+// device status is set.  Vectors of type T; the operator is A.
 template <typename T>
 mxs_status cg_loop(mxs_ctx* ctx, const mxs_matrix* A, Work& w, T* x, T* r, T* p, T* q,
                    int check_every) {
   const int64_t n = A->n;
   const int g = red_grid(n);
   const T one = 1, zero = 0;
-  return run_polled(ctx, w, w.hst->iters, check_every, "CG", [&](int64_t k0) -> mxs_status {
-    for (int64_t kk = k0; kk < k0 + check_every; ++kk) {
-      const int par = (int)(kk & 1);
-      // q = A p and p.q: in the product's own launches when its kernel
-      // offers that, else a separate reduction
-      const double* pq = w.pw;
-      int gq = launch_spmv_dot(ctx, A, p, q, &w.st->done, w.pw);
-      if (gq == 0) {
-        mxs_status s = launch_spmv(ctx, A, &one, p, &zero, q, &w.st->done);
-        if (s) return s;
-        k_cg_pq<T><<<g, RB, 0, ctx->stream>>>(n, p, q, w.pa, w.st);
-        pq = w.pa;
-        gq = g;
-      }
-      k_cg_r<T><<<g, RB, 0, ctx->stream>>>(n, r, q, pq, gq, w.pb, w.st, par, kk);
-      k_cg_xp<T><<<g, RB, 0, ctx->stream>>>(n, x, r, p, w.pb, g, w.st, par, kk);
+  return run_polled(ctx, w, w.hst->iters, check_every, "CG", [&](int64_t kk) -> mxs_status {
+    const int par = (int)(kk & 1);
+    // q = A p and p.q: in the product's own launches when its kernel
+    // offers that, else a separate reduction
+    const double* pq = w.pw;
+    int gq = launch_spmv_dot(ctx, A, p, q, &w.st->done, w.pw);
+    if (gq == 0) {
+      mxs_status s = launch_spmv(ctx, A, &one, p, &zero, q, &w.st->done);
+      if (s) return s;
+      k_cg_pq<T><<<g, RB, 0, ctx->stream>>>(n, p, q, w.pa, w.st);
+      pq = w.pa;
+      gq = g;
     }
+    k_cg_r<T><<<g, RB, 0, ctx->stream>>>(n, r, q, pq, gq, w.pb, w.st, par, kk);
+    k_cg_xp<T><<<g, RB, 0, ctx->stream>>>(n, x, r, p, w.pb, g, w.st, par, kk);
     MXS_HIP_TRY(ctx, hipGetLastError());
     return MXS_OK;
   });
@@ -1650,19 +1698,17 @@ mxs_status pcg_loop(mxs_ctx* ctx, const mxs_matrix* A, const mxs_precond* M, con
   const int64_t n = A->n;
   const int g = red_grid(n);
   const T one = 1, zero = 0;
-  return run_polled(ctx, w, w.hst->iters, check_every, "PCG", [&](int64_t k0) -> mxs_status {
-    for (int64_t k = k0; k < k0 + check_every; ++k) {
-      const int par = (int)(k & 1);
-      mxs_status s = launch_spmv(ctx, A, &one, p, &zero, q, &w.st->done);
-      if (s) return s;
-      k_cg_pq<T><<<g, RB, 0, ctx->stream>>>(n, p, q, w.pa, w.st);
-      k_pcg_update<T, PC><<<g, RB, 0, ctx->stream>>>(n, x, p, r, q, mv, w.pa, g, w.pb, w.st,
-                                                     par);
-      if (PC == 2)
-        k_bj_apply<T><<<g, RB, 0, ctx->stream>>>(n, M->bs, mv, r, z, w.pc, w.st);
-      k_pcg_direction<T, PC><<<g, RB, 0, ctx->stream>>>(n, r, p, z, mv, w.pb, w.pc, g, w.st,
-                                                        par, k);
-    }
+  return run_polled(ctx, w, w.hst->iters, check_every, "PCG", [&](int64_t k) -> mxs_status {
+    const int par = (int)(k & 1);
+    mxs_status s = launch_spmv(ctx, A, &one, p, &zero, q, &w.st->done);
+    if (s) return s;
+    k_cg_pq<T><<<g, RB, 0, ctx->stream>>>(n, p, q, w.pa, w.st);
+    k_pcg_update<T, PC><<<g, RB, 0, ctx->stream>>>(n, x, p, r, q, mv, w.pa, g, w.pb, w.st,
+                                                   par);
+    if (PC == 2)
+      k_bj_apply<T><<<g, RB, 0, ctx->stream>>>(n, M->bs, mv, r, z, w.pc, w.st);
+    k_pcg_direction<T, PC><<<g, RB, 0, ctx->stream>>>(n, r, p, z, mv, w.pb, w.pc, g, w.st,
+                                                      par, k);
     MXS_HIP_TRY(ctx, hipGetLastError());
     return MXS_OK;
   });
@@ -1804,35 +1850,33 @@ mxs_status solve_bicgstab(mxs_ctx* ctx, const mxs_matrix* A, const double* b, do
     }
     bool first = true;
     while (done == RUN) {
-      s = run_polled(ctx, w, iters, stop.check_every, "BiCGSTAB", [&](int64_t k0) -> mxs_status {
-        for (int64_t k = k0; k < k0 + stop.check_every; ++k) {
-          const int par = (int)(k & 1);
-          k_bi_p<<<g, RB, 0, ctx->stream>>>(n, r, p, v, w.pc, g, w.st, par, k, first ? 1 : 0);
-          first = false;
-          mxs_status e;
-          // v = A p with r_hat.v formed by the product when its kernel can
-          // (rows from LDS), else a separate reduction
-          const double* pv = w.pw;
-          int gv = launch_spmv_dot(ctx, A, p, v, &w.st->done, w.pw, rh, 1);
-          if (gv == 0) {
-            if ((e = launch_spmv(ctx, A, &one, p, &zero, v, &w.st->done))) return e;
-            k_bi_rv<<<g, RB, 0, ctx->stream>>>(n, rh, v, w.pa, w.st);
-            pv = w.pa;
-            gv = g;
-          }
-          k_bi_s<<<g, RB, 0, ctx->stream>>>(n, r, v, sv, pv, gv, w.pb, w.st, par);
-          // t = A s with t.s and t.t formed by the product (the half-step
-          // test then moves into k_bi_update), else k_bi_omega forms them
-          int gt = launch_spmv_dot(ctx, A, sv, t, &w.st->done, w.pm, nullptr, 2);
-          if (gt == 0) {
-            if ((e = launch_spmv(ctx, A, &one, sv, &zero, t, &w.st->done))) return e;
-            k_bi_omega<<<g, RB, 0, ctx->stream>>>(n, t, sv, w.pb, g, w.pd, w.st, k);
-            k_bi_update<<<g, RB, 0, ctx->stream>>>(n, x, p, sv, t, r, rh, w.pd, g, w.pc, w.st,
-                                                   k, 0, w.pb, g);
-          } else {
-            k_bi_update<<<g, RB, 0, ctx->stream>>>(n, x, p, sv, t, r, rh, w.pm, gt, w.pc, w.st,
-                                                   k, 1, w.pb, g);
-          }
+      s = run_polled(ctx, w, iters, stop.check_every, "BiCGSTAB", [&](int64_t k) -> mxs_status {
+        const int par = (int)(k & 1);
+        k_bi_p<<<g, RB, 0, ctx->stream>>>(n, r, p, v, w.pc, g, w.st, par, k, first ? 1 : 0);
+        first = false;
+        mxs_status e;
+        // v = A p with r_hat.v formed by the product when its kernel can
+        // (rows from LDS), else a separate reduction
+        const double* pv = w.pw;
+        int gv = launch_spmv_dot(ctx, A, p, v, &w.st->done, w.pw, rh, 1);
+        if (gv == 0) {
+          if ((e = launch_spmv(ctx, A, &one, p, &zero, v, &w.st->done))) return e;
+          k_bi_rv<<<g, RB, 0, ctx->stream>>>(n, rh, v, w.pa, w.st);
+          pv = w.pa;
+          gv = g;
+        }
+        k_bi_s<<<g, RB, 0, ctx->stream>>>(n, r, v, sv, pv, gv, w.pb, w.st, par);
+        // t = A s with t.s and t.t formed by the product (the half-step
+        // test then moves into k_bi_update), else k_bi_omega forms them
+        int gt = launch_spmv_dot(ctx, A, sv, t, &w.st->done, w.pm, nullptr, 2);
+        if (gt == 0) {
+          if ((e = launch_spmv(ctx, A, &one, sv, &zero, t, &w.st->done))) return e;
+          k_bi_omega<<<g, RB, 0, ctx->stream>>>(n, t, sv, w.pb, g, w.pd, w.st, k);
+          k_bi_update<<<g, RB, 0, ctx->stream>>>(n, x, p, sv, t, r, rh, w.pd, g, w.pc, w.st,
+                                                 k, 0, w.pb, g);
+        } else {
+          k_bi_update<<<g, RB, 0, ctx->stream>>>(n, x, p, sv, t, r, rh, w.pm, gt, w.pc, w.st,
+                                                 k, 1, w.pb, g);
         }
         MXS_HIP_TRY(ctx, hipGetLastError());
         return MXS_OK;
@@ -1960,15 +2004,13 @@ mxs_status solve_pipecg(mxs_ctx* ctx, const mxs_matrix* A, const double* b, doub
   for (;;) {
     if (h.done == RUN) {
       s = run_polled(ctx, w, h.iters, stop.check_every, "pipelined CG",
-                     [&](int64_t k0) -> mxs_status {
-                       for (int64_t k = k0; k < k0 + stop.check_every; ++k) {
-                         double* pin = (k & 1) ? w.pb : w.pa;
-                         double* pout = (k & 1) ? w.pa : w.pb;
-                         mxs_status e = launch_spmv(ctx, A, &one, wv, &zero, q, &w.st->done);
-                         if (e) return e;
-                         k_pipe_update<<<g, RB, 0, ctx->stream>>>(n, x, r, wv, q, z, sv, p, pin,
-                                                                  g, pout, w.st, k);
-                       }
+                     [&](int64_t k) -> mxs_status {
+                       double* pin = (k & 1) ? w.pb : w.pa;
+                       double* pout = (k & 1) ? w.pa : w.pb;
+                       mxs_status e = launch_spmv(ctx, A, &one, wv, &zero, q, &w.st->done);
+                       if (e) return e;
+                       k_pipe_update<<<g, RB, 0, ctx->stream>>>(n, x, r, wv, q, z, sv, p, pin,
+                                                                g, pout, w.st, k);
                        MXS_HIP_TRY(ctx, hipGetLastError());
                        return MXS_OK;
                      });
@@ -2050,24 +2092,22 @@ mxs_status solve_cgs(mxs_ctx* ctx, const mxs_matrix* A, const double* b, double*
       if ((s = push_state(ctx, w))) return s;
     }
     if (done == RUN) {
-      s = run_polled(ctx, w, iters, stop.check_every, "CGS", [&](int64_t k0) -> mxs_status {
-        for (int64_t k = k0; k < k0 + stop.check_every; ++k) {
-          const int par = (int)(k & 1);
-          mxs_status e;
-          // v = A p with r_hat.v formed by the product when its kernel can
-          const double* ps = w.pw;
-          int gs = launch_spmv_dot(ctx, A, p, v, &w.st->done, w.pw, rh, 1);
-          if (gs == 0) {
-            if ((e = launch_spmv(ctx, A, &one, p, &zero, v, &w.st->done))) return e;
-            k_cgs_sigma<<<g, RB, 0, ctx->stream>>>(n, rh, v, w.pa, w.st);
-            ps = w.pa;
-            gs = g;
-          }
-          k_cgs_qw<<<g, RB, 0, ctx->stream>>>(n, u, v, q, wv, x, ps, gs, w.st, par);
-          if ((e = launch_spmv(ctx, A, &one, wv, &zero, v, &w.st->done))) return e;
-          k_cgs_r<<<g, RB, 0, ctx->stream>>>(n, r, v, rh, w.pb, w.st);
-          k_cgs_dir<<<g, RB, 0, ctx->stream>>>(n, r, q, u, p, w.pb, g, w.st, par, k);
+      s = run_polled(ctx, w, iters, stop.check_every, "CGS", [&](int64_t k) -> mxs_status {
+        const int par = (int)(k & 1);
+        mxs_status e;
+        // v = A p with r_hat.v formed by the product when its kernel can
+        const double* ps = w.pw;
+        int gs = launch_spmv_dot(ctx, A, p, v, &w.st->done, w.pw, rh, 1);
+        if (gs == 0) {
+          if ((e = launch_spmv(ctx, A, &one, p, &zero, v, &w.st->done))) return e;
+          k_cgs_sigma<<<g, RB, 0, ctx->stream>>>(n, rh, v, w.pa, w.st);
+          ps = w.pa;
+          gs = g;
         }
+        k_cgs_qw<<<g, RB, 0, ctx->stream>>>(n, u, v, q, wv, x, ps, gs, w.st, par);
+        if ((e = launch_spmv(ctx, A, &one, wv, &zero, v, &w.st->done))) return e;
+        k_cgs_r<<<g, RB, 0, ctx->stream>>>(n, r, v, rh, w.pb, w.st);
+        k_cgs_dir<<<g, RB, 0, ctx->stream>>>(n, r, q, u, p, w.pb, g, w.st, par, k);
         MXS_HIP_TRY(ctx, hipGetLastError());
         return MXS_OK;
       });
@@ -2166,13 +2206,18 @@ mxs_status solve_gmres(mxs_ctx* ctx, const mxs_matrix* A, const double* b, doubl
                   (long long)h.iters, beta / base);
     }
     const int64_t before = h.iters;
+    int64_t seen;
+    bool ended = false;
+    mail_reset(w, before);
     k_gm_reset<<<1, 1, 0, ctx->stream>>>(w.st);
     k_gm_start<<<g, RB, 0, ctx->stream>>>(n, r, V, w.st);
-    for (int j = 0; j < m; ++j) {
+    for (int j = 0; j < m && !ended; ++j) {
       double* vj = V + (size_t)j * ld;
       if ((s = launch_spmv(ctx, A, &one, vj, &zero, wv, &w.st->cycle))) return s;
       gm_passes(ctx, g, n, ld, j, V, wv, w);
       k_gm_scale<<<g, RB, 0, ctx->stream>>>(n, wv, V + (size_t)(j + 1) * ld, w.st);
+      MXS_HIP_TRY(ctx, hipGetLastError());
+      if ((s = await_iters(ctx, w, before + j + 1 - kAhead, &seen, &ended, "GMRES"))) return s;
     }
     k_gm_backsolve<<<1, RB, 0, ctx->stream>>>(w.st);
     k_gm_xupdate<<<g, RB, 0, ctx->stream>>>(n, ld, V, x, w.st);
@@ -2483,23 +2528,16 @@ mxs_status mxs_pagerank(mxs_ctx* ctx, const mxs_graph* G, const mxs_matrix* op, 
   if ((s = push_state(ctx, w))) return s;
   k_pr_init<<<g, RB, 0, ctx->stream>>>(n, x, G->dangling, w.pa);
   const double one = 1.0, zero = 0.0;
-  int64_t k = 0;
-  const int check_every = 16;
-  while (h.done == RUN) {
-    const int64_t before = k;
-    for (int it = 0; it < check_every; ++it, ++k) {
-      double* pin = (k & 1) ? w.pb : w.pa;
-      double* pout = (k & 1) ? w.pa : w.pb;
-      if ((s = launch_spmv(ctx, T, &one, x, &zero, z, &w.st->done))) return s;
-      k_pr_update<<<g, RB, 0, ctx->stream>>>(n, x, z, G->dangling, damping, pin, g, pout, w.st,
-                                             k);
-    }
+  s = run_polled(ctx, w, 0, 16, "PageRank", [&](int64_t k) -> mxs_status {
+    double* pin = (k & 1) ? w.pb : w.pa;
+    double* pout = (k & 1) ? w.pa : w.pb;
+    mxs_status e = launch_spmv(ctx, T, &one, x, &zero, z, &w.st->done);
+    if (e) return e;
+    k_pr_update<<<g, RB, 0, ctx->stream>>>(n, x, z, G->dangling, damping, pin, g, pout, w.st, k);
     MXS_HIP_TRY(ctx, hipGetLastError());
-    if ((s = pull_state(ctx, w))) return s;
-    if (h.done == RUN && h.iters <= before)
-      return fail(ctx, MXS_HIP, "PageRank made no progress (device state not updated)");
-    k = h.iters;
-  }
+    return MXS_OK;
+  });
+  if (s) return s;
   const mxs_status res = h.done == ST_CONVERGED ? MXS_OK
                          : h.done == ST_MAXIT   ? MXS_NOT_CONVERGED
                                                 : MXS_NONFINITE;
