@@ -1104,7 +1104,7 @@ __global__ __launch_bounds__(RB) void k_cgs_dir(int64_t n, const double* __restr
 // Preconditioned CG (Saad 2003, Algorithm 9.1), PC = 1 Jacobi (z = dinv r,
 // never stored: formed where it is used), PC = 2 block Jacobi (z stored).
 // Iteration k (par = k & 1), rho[par] = (r, z) of the previous step:
-//   q = A p;  k_cg_pq: partials of p.q;
+//   q = A p and partials of p.q (the product's own, else k_cg_pq);
 //   k_pcg_update: alpha = rho[par] / (p.q), x += alpha p, r -= alpha q,
 //                 partials of (r.z, r.r) (Jacobi) or r.r (block);
 //   [block: k_bj_apply: z = M^{-1} r, partials of r.z]
@@ -1164,29 +1164,36 @@ __global__ __launch_bounds__(RB) void k_pcg_update(int64_t n, T* __restrict__ x,
                                                    double* __restrict__ pb, KState* st, int par) {
   if (st->done) return;
   double pq[1];
-  finish<1>(pa, g, pq);
-  if (!isfinite(pq[0]) || pq[0] <= 0.0) {
-    if (lead()) stop_with(st, isfinite(pq[0]) ? ST_BREAKDOWN : ST_NONFINITE);
-    return;
-  }
-  const double alpha = st->rho[par] / pq[0];
-  if (lead()) st->alpha = alpha;
-  const T a = (T)alpha;
+  bool broke = false;
+  T a = 0;
   double acc[2] = {0.0, 0.0};
   // e = (x, p, r, q, dinv); block Jacobi reads no dinv
   const auto use = [&](int64_t i, const Pack<T, 5>& e) {
+    if (broke) return;
     x[i] = e.v[0] + a * e.v[1];
     const T ri = e.v[2] - a * e.v[3];
     r[i] = ri;
     if (PC == 1) acc[1] += (double)ri * (double)(e.v[4] * ri);
     acc[0] += (double)ri * (double)ri;
   };
-  strided4(
+  strided4_pre(
       n,
       [&](int64_t i) {
         return Pack<T, 5>{{x[i], p[i], r[i], q[i], PC == 1 ? dinv[i] : T(0)}};
       },
+      [&]() {
+        finish_wide<1>(pa, g, pq);  // the product's partials when it formed p.q
+        broke = !isfinite(pq[0]) || pq[0] <= 0.0;
+        if (broke) {
+          if (lead()) stop_with(st, isfinite(pq[0]) ? ST_BREAKDOWN : ST_NONFINITE);
+          return;
+        }
+        const double alpha = st->rho[par] / pq[0];
+        if (lead()) st->alpha = alpha;
+        a = (T)alpha;
+      },
       use);
+  if (broke) return;
   if (PC == 1) {
     block_partials<2>(acc, pb);
   } else {
@@ -1700,11 +1707,19 @@ mxs_status pcg_loop(mxs_ctx* ctx, const mxs_matrix* A, const mxs_precond* M, con
   const T one = 1, zero = 0;
   return run_polled(ctx, w, w.hst->iters, check_every, "PCG", [&](int64_t k) -> mxs_status {
     const int par = (int)(k & 1);
-    mxs_status s = launch_spmv(ctx, A, &one, p, &zero, q, &w.st->done);
-    if (s) return s;
-    k_cg_pq<T><<<g, RB, 0, ctx->stream>>>(n, p, q, w.pa, w.st);
-    k_pcg_update<T, PC><<<g, RB, 0, ctx->stream>>>(n, x, p, r, q, mv, w.pa, g, w.pb, w.st,
-                                                   par);
+    // as in CG: p.q in the product's own launches when its kernel offers that
+    // (Jacobi CG on 2^20 power-law rows, a solve: 4.24 ms with the separate
+    // reduction, 4.11 so)
+    const double* pq = w.pw;
+    int gq = launch_spmv_dot(ctx, A, p, q, &w.st->done, w.pw);
+    if (gq == 0) {
+      mxs_status s = launch_spmv(ctx, A, &one, p, &zero, q, &w.st->done);
+      if (s) return s;
+      k_cg_pq<T><<<g, RB, 0, ctx->stream>>>(n, p, q, w.pa, w.st);
+      pq = w.pa;
+      gq = g;
+    }
+    k_pcg_update<T, PC><<<g, RB, 0, ctx->stream>>>(n, x, p, r, q, mv, pq, gq, w.pb, w.st, par);
     if (PC == 2)
       k_bj_apply<T><<<g, RB, 0, ctx->stream>>>(n, M->bs, mv, r, z, w.pc, w.st);
     k_pcg_direction<T, PC><<<g, RB, 0, ctx->stream>>>(n, r, p, z, mv, w.pb, w.pc, g, w.st,
