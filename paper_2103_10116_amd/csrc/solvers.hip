@@ -60,6 +60,7 @@ struct KState {
   double est;       // GMRES residual estimate |g_{k}|
   double H[(MAXM + 1) * MAXM];  // column-major, leading dimension MAXM+1
   double cs[MAXM], sn[MAXM], g[MAXM + 1], y[MAXM], h2[MAXM + 1];
+  double sc[MAXM + 1];  // v_i = sc[i] times the i-th stored vector
   // pipelined CG: gamma and alpha by iteration parity, and the iteration
   // that starts a recurrence (beta = 0, gamma and delta from dot[])
   double pg[2], palpha[2];
@@ -647,22 +648,31 @@ __global__ __launch_bounds__(RB) void k_bi_half(int64_t n, double* __restrict__ 
 // GMRES(m): classical Gram-Schmidt with one reorthogonalisation pass.  The
 // multi-dot partials of (j+1) values per block are finished by a one-block
 // kernel that also owns the small dense work (Hessenberg column, Givens).
+// The basis is stored as it arises, u_0 = r and u_{j+1} = the orthogonalised
+// A v_j, with its scales beside it (v_i = sc[i] u_i): the passes apply them
+// to the coefficients and to A u_j as they read it (GMRES(30) on the 100^3
+// convection-diffusion grid: 16.77 ms with a pass of its own that scales and
+// a copy of r, 16.24 so).
 // ---------------------------------------------------------------------------
 // The three passes over the basis are instantiated for JB = 8, 16 and 32
 // vectors (the smallest that holds v_0..v_j), so that short bases do not pay
 // registers, and occupancy, for 32.
-// partials of V(:,0..j)^T w
+// partials of U(:,0..j)^T w, w = A v_j = sc[j] z
 template <int JB>
 __global__ __launch_bounds__(RB) void k_gm_dots(int64_t n, int64_t ldv, int j,
                                                 const double* __restrict__ V,
-                                                const double* __restrict__ w,
-                                                double* __restrict__ part, const KState* st) {
+                                                const double* __restrict__ z,
+                                                double* __restrict__ part, KState* st) {
+  // (reports what k_gm_fin decided: that one-block kernel would end only when
+  // the store had reached the host, 2 us)
+  if (lead()) post(st, st->iters, st->done | (st->cycle ? MAIL_CYCLE : 0));
   if (st->done || st->cycle) return;
+  const double sj = st->sc[j];
   double acc[JB];
 #pragma unroll
   for (int i = 0; i < JB; ++i) acc[i] = 0.0;
   GRID_STRIDE(r, n) {
-    const double wr = w[r];
+    const double wr = sj * z[r];
     double vr[JB];
 #pragma unroll
     for (int i = 0; i < JB; ++i) vr[i] = i <= j ? V[i * ldv + r] : 0.0;
@@ -672,23 +682,27 @@ __global__ __launch_bounds__(RB) void k_gm_dots(int64_t n, int64_t ldv, int j,
   block_partials_m<JB>(acc, part);
 }
 
-// w -= V h (first-pass coefficients); partials of V^T w on the updated rows
+// w = A v_j - V h (first-pass coefficients); partials of U^T w
 template <int JB>
 __global__ __launch_bounds__(RB) void k_gm_orth(int64_t n, int64_t ldv, int j,
                                                 const double* __restrict__ V,
+                                                const double* __restrict__ z,
                                                 double* __restrict__ w,
                                                 double* __restrict__ part, const KState* st) {
   if (st->done || st->cycle) return;
   __shared__ double h[JB];
   if (threadIdx.x < JB)
-    h[threadIdx.x] = (int)threadIdx.x <= j ? st->H[j * (MAXM + 1) + threadIdx.x] : 0.0;
+    h[threadIdx.x] = (int)threadIdx.x <= j
+                         ? st->H[j * (MAXM + 1) + threadIdx.x] * st->sc[threadIdx.x]
+                         : 0.0;
   __syncthreads();
+  const double sj = st->sc[j];
   double acc[JB];
 #pragma unroll
   for (int i = 0; i < JB; ++i) acc[i] = 0.0;
   GRID_STRIDE(r, n) {
     double vr[JB];
-    double wr = w[r];
+    double wr = sj * z[r];
 #pragma unroll
     for (int i = 0; i < JB; ++i) {
       vr[i] = i <= j ? V[i * ldv + r] : 0.0;
@@ -709,7 +723,9 @@ __global__ __launch_bounds__(RB) void k_gm_norm(int64_t n, int64_t ldv, int j,
                                                 double* __restrict__ part, const KState* st) {
   if (st->done || st->cycle) return;
   __shared__ double h[JB];
-  if (threadIdx.x < JB) h[threadIdx.x] = (int)threadIdx.x <= j ? st->h2[threadIdx.x] : 0.0;
+  if (threadIdx.x < JB)
+    h[threadIdx.x] =
+        (int)threadIdx.x <= j ? st->h2[threadIdx.x] * st->sc[threadIdx.x] : 0.0;
   __syncthreads();
   double acc[1] = {0.0};
   GRID_STRIDE(r, n) {
@@ -734,8 +750,9 @@ __global__ __launch_bounds__(RB) void k_gm_fin(const double* __restrict__ part, 
   const int L = MAXM + 1;
   double* Hj = st->H + j * L;
   if (stage < 3) {
-    const double out = finish_m(part, g);
     const int i = threadIdx.x;
+    const double sc = i <= j ? st->sc[i] : 0.0;
+    const double out = finish_m(part, g) * sc;
     if (i <= j) {
       if (stage == 1) {
         Hj[i] = out;
@@ -787,7 +804,8 @@ __global__ __launch_bounds__(RB) void k_gm_fin(const double* __restrict__ part, 
         const double est = fabs(gg[1]);
         st->k = j + 1;
         st->est = est;
-        st->res2 = hn;  // h_{j+1,j} for the scaling kernel
+        st->res2 = hn;
+        st->sc[j + 1] = 1.0 / hn;
         st->cs[j] = c_[j];
         st->sn[j] = s_[j];
         st->g[j] = gg[0];
@@ -800,18 +818,6 @@ __global__ __launch_bounds__(RB) void k_gm_fin(const double* __restrict__ part, 
   }
   __syncthreads();
   if (verdict == 0 && t <= j + 1) Hj[t] = hc[t];
-}
-
-// v_{j+1} = w / h_{j+1,j}.  Reports what k_gm_fin has decided: that one-block
-// kernel would end only when the store has reached the host (2 us).
-__global__ __launch_bounds__(RB) void k_gm_scale(int64_t n, const double* __restrict__ w,
-                                                 double* __restrict__ vn, KState* st) {
-  if (lead()) post(st, st->iters, st->done | (st->cycle ? MAIL_CYCLE : 0));
-  if (st->done || st->cycle) return;
-  const double inv = 1.0 / st->res2;
-  strided4(
-      n, [&](int64_t i) { return Pack<double, 1>{{w[i]}}; },
-      [&](int64_t i, const Pack<double, 1>& e) { vn[i] = e.v[0] * inv; });
 }
 
 // back substitution R y = g: the triangle is staged in LDS by all threads,
@@ -841,7 +847,8 @@ __global__ __launch_bounds__(RB) void k_gm_xupdate(int64_t n, int64_t ldv,
   if (st->done) return;
   __shared__ double y[MAXM];
   const int k = st->k;
-  if (threadIdx.x < MAXM) y[threadIdx.x] = (int)threadIdx.x < k ? st->y[threadIdx.x] : 0.0;
+  if (threadIdx.x < MAXM)
+    y[threadIdx.x] = (int)threadIdx.x < k ? st->y[threadIdx.x] * st->sc[threadIdx.x] : 0.0;
   __syncthreads();
   GRID_STRIDE(r, n) {
     double xr = x[r];
@@ -852,22 +859,14 @@ __global__ __launch_bounds__(RB) void k_gm_xupdate(int64_t n, int64_t ldv,
   }
 }
 
-// v_0 = r / beta with beta = sqrt(dot[0]); the one-block kernel below
-// resets the cycle state first
+// starts a cycle: u_0 = r is in place, v_0 = r / beta with beta = sqrt(dot[0])
 __global__ void k_gm_reset(KState* st) {
   const double beta = sqrt(st->dot[0]);
   for (int i = 0; i <= MAXM; ++i) st->g[i] = 0.0;
   st->g[0] = beta;
+  st->sc[0] = 1.0 / beta;
   st->k = 0;
   st->cycle = 0;
-}
-
-__global__ __launch_bounds__(RB) void k_gm_start(int64_t n, const double* __restrict__ r,
-                                                 double* __restrict__ v0, const KState* st) {
-  const double inv = 1.0 / st->g[0];
-  strided4(
-      n, [&](int64_t i) { return Pack<double, 1>{{r[i]}}; },
-      [&](int64_t i, const Pack<double, 1>& e) { v0[i] = e.v[0] * inv; });
 }
 
 // ---------------------------------------------------------------------------
@@ -2159,25 +2158,26 @@ mxs_status solve_cgs(mxs_ctx* ctx, const mxs_matrix* A, const double* b, double*
 
 // the three Gram-Schmidt passes of step j and their finishing kernels
 template <int JB>
-void gm_passes_jb(mxs_ctx* ctx, int g, int64_t n, size_t ld, int j, const double* V,
-                  double* wv, const Work& w) {
-  k_gm_dots<JB><<<g, RB, 0, ctx->stream>>>(n, ld, j, V, wv, w.pm, w.st);
+void gm_passes_jb(mxs_ctx* ctx, int g, int64_t n, size_t ld, int j, double* V,
+                  const double* z, const Work& w) {
+  double* wv = V + (size_t)(j + 1) * ld;
+  k_gm_dots<JB><<<g, RB, 0, ctx->stream>>>(n, ld, j, V, z, w.pm, w.st);
   k_gm_fin<<<1, RB, 0, ctx->stream>>>(w.pm, g, j, 1, w.st);
-  k_gm_orth<JB><<<g, RB, 0, ctx->stream>>>(n, ld, j, V, wv, w.pm, w.st);
+  k_gm_orth<JB><<<g, RB, 0, ctx->stream>>>(n, ld, j, V, z, wv, w.pm, w.st);
   k_gm_fin<<<1, RB, 0, ctx->stream>>>(w.pm, g, j, 2, w.st);
   k_gm_norm<JB><<<g, RB, 0, ctx->stream>>>(n, ld, j, V, wv, w.pa, w.st);
   k_gm_fin<<<1, RB, 0, ctx->stream>>>(w.pa, g, j, 3, w.st);
 }
 
-void gm_passes(mxs_ctx* ctx, int g, int64_t n, size_t ld, int j, const double* V, double* wv,
+void gm_passes(mxs_ctx* ctx, int g, int64_t n, size_t ld, int j, double* V, const double* z,
                const Work& w) {
   static_assert(MAXM == 32, "buckets of 8, 16 and 32 basis vectors");
   if (j < 8)
-    gm_passes_jb<8>(ctx, g, n, ld, j, V, wv, w);
+    gm_passes_jb<8>(ctx, g, n, ld, j, V, z, w);
   else if (j < 16)
-    gm_passes_jb<16>(ctx, g, n, ld, j, V, wv, w);
+    gm_passes_jb<16>(ctx, g, n, ld, j, V, z, w);
   else
-    gm_passes_jb<32>(ctx, g, n, ld, j, V, wv, w);
+    gm_passes_jb<32>(ctx, g, n, ld, j, V, z, w);
 }
 
 mxs_status solve_gmres(mxs_ctx* ctx, const mxs_matrix* A, const double* b, double* x,
@@ -2187,11 +2187,11 @@ mxs_status solve_gmres(mxs_ctx* ctx, const mxs_matrix* A, const double* b, doubl
   const int64_t n = A->n;
   const size_t ld = align_up((size_t)n, 64);
   Work w;
-  mxs_status s = get_work(ctx, (size_t)(m + 3) * ld * sizeof(double), &w);
+  mxs_status s = get_work(ctx, (size_t)(m + 2) * ld * sizeof(double), &w);
   if (s) return s;
   double* V = (double*)w.vec;  // m+1 basis vectors
-  double* wv = V + (size_t)(m + 1) * ld;
-  double* r = wv + ld;
+  double* z = V + (size_t)(m + 1) * ld;
+  double* r = V;               // a cycle's first one is the residual
   double nb2, nr2;
   if ((s = residual(ctx, A, b, x, r))) return s;
   if ((s = dots<double>(ctx, w, n, b, b, r, r, &nb2, &nr2))) return s;
@@ -2225,12 +2225,10 @@ mxs_status solve_gmres(mxs_ctx* ctx, const mxs_matrix* A, const double* b, doubl
     bool ended = false;
     mail_reset(w, before);
     k_gm_reset<<<1, 1, 0, ctx->stream>>>(w.st);
-    k_gm_start<<<g, RB, 0, ctx->stream>>>(n, r, V, w.st);
     for (int j = 0; j < m && !ended; ++j) {
       double* vj = V + (size_t)j * ld;
-      if ((s = launch_spmv(ctx, A, &one, vj, &zero, wv, &w.st->cycle))) return s;
-      gm_passes(ctx, g, n, ld, j, V, wv, w);
-      k_gm_scale<<<g, RB, 0, ctx->stream>>>(n, wv, V + (size_t)(j + 1) * ld, w.st);
+      if ((s = launch_spmv(ctx, A, &one, vj, &zero, z, &w.st->cycle))) return s;
+      gm_passes(ctx, g, n, ld, j, V, z, w);
       MXS_HIP_TRY(ctx, hipGetLastError());
       if ((s = await_iters(ctx, w, before + j + 1 - kAhead, &seen, &ended, "GMRES"))) return s;
     }
