@@ -189,6 +189,7 @@ struct CooPart {
   // AUTO for irregular matrices: the two-pass product over its own copy of
   // the entries (the arrays above are then kept for export only)
   BinPart bin;
+  bool bin_all = false;  // HYB: `bin` holds the ELL part's entries too
   DiagPart diag;  // as for CSR
 };
 

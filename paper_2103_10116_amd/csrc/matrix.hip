@@ -1528,12 +1528,24 @@ mxs_status convert_typed(mxs_ctx* ctx, const mxs_matrix* S, mxs_matrix* A, mxs_f
   const int req = opts ? opts->col_panels : 0;
   const int P = (cnnz > 0 && (req > 1 || (req == 0 && Kmax > 64))) ? merge_panels(A, opts) : 1;
   if (no_kernel_asked(opts) && Kmax > 64 && bins_fit(ctx, n, A->ncols, cnnz, Kmax - K, A->dt)) {
-    if (mxs_status st = hyb_bins(ctx, A, off)) return st;
+    // an ELL part of at most a quarter of the entries goes into the bins too:
+    // its launch reads x at random once more and leaves y to be read back
+    // (10^6 rows, s = 2.0, one slot a row, FP32: 34.3 us with it, 26.8 without).
+    // A larger one may hold rows whose columns are near each other, which it
+    // reads faster than two passes do.
+    if (K > 0 && 4 * cnnz >= 3 * nnz && bins_fit(ctx, n, A->ncols, nnz, Kmax, A->dt)) {
+      if (mxs_status st = coo_bins<V>(ctx, S, A, d_err)) return st;
+      A->coo.bin_all = A->coo.bin.on();
+    } else if (mxs_status st = hyb_bins(ctx, A, off)) {
+      return st;
+    }
   }
   if (P > 1) {
     if (mxs_status st = hyb_coo_panels<V>(ctx, A, P, off)) return st;
     return setup_coo_part(ctx, A, A->coo, cnnz, std::max<int64_t>(Kmax - K, 0), vb, bnnz,
-                          A->coo.bin.on() && K == 0 ? empty : std::vector<int32_t>(), opts);
+                          A->coo.bin.on() && (K == 0 || A->coo.bin_all) ? empty
+                                                                        : std::vector<int32_t>(),
+                          opts);
   }
   return setup_coo_part(ctx, A, A->coo, cnnz, std::max<int64_t>(Kmax - K, 0), vb, bnnz,
                         empty, opts);

@@ -1971,7 +1971,7 @@ void launch_typed(mxs_ctx* ctx, const mxs_matrix* A, T alpha, const T* x, T beta
       launch_ell<V, T>(ctx, A, alpha, x, beta, y, skip);
       break;
     case MXS_HYB:
-      if (A->ell.K == 0) {
+      if (A->ell.K == 0 || A->coo.bin_all) {
         launch_coo<V, T, false>(ctx, A->coo, A->n, alpha, x, beta, y, skip, scratch, bytes);
       } else {
         launch_ell<V, T>(ctx, A, alpha, x, beta, y, skip);

@@ -147,3 +147,35 @@ def test_values_refreshed_in_place(env, orc):
     r = mxs.pagerank(ctx, g, x, 0.85, 1e-12)
     assert st == orc.OK and r.status == mxs.OK
     assert np.abs(x.cpu().numpy() - xo).sum() <= 1e-12
+
+
+@pytest.mark.parametrize("short", [0, 500])
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+def test_hyb_whole_rows(env, orc, dt, short):
+    """A hybrid whose ELL part (one slot a row) holds just under and just over
+    a quarter of the entries: the products of whole rows and of the COO part's,
+    with rows without entries."""
+    mxs, ctx, torch = env
+    lens = [4, 4, 0, 4] * 70000 + [100] + [1] * short
+    A = _matrix(40000, lens, 31)
+    ell = int((np.asarray(lens) > 0).sum())
+    assert (4 * (A.nnz - ell) >= 3 * A.nnz) == (short == 0)
+    B = mxs.Matrix.from_host(ctx, A).convert("hyb", dt, ell_width=1)
+    assert B.info()["ell_width"] == 1 and B.info()["coo_nnz"] == A.nnz - ell
+    tdt = torch.float64 if dt == "f64" else torch.float32
+    tol = 1e-13 if dt == "f64" else 1e-5
+    x, y0, val = I.uniform_vector(40000, 32), I.uniform_vector(A.n, 33), A.val
+    if dt == "f32":
+        x, y0, val = (v.astype(np.float32).astype(np.float64) for v in (x, y0, val))
+    R = I.CSRMatrix(A.n, 40000, A.rowptr, A.col, val)
+    xd = torch.from_numpy(x).to(tdt).cuda()
+    for beta in (0.0, -0.5):
+        ya = torch.from_numpy(y0).to(tdt).cuda()
+        if beta == 0.0:
+            ya.fill_(float("nan"))
+        yb = ya.clone()
+        mxs.spmv(ctx, B, xd, ya, 1.5, beta)
+        mxs.spmv(ctx, B, xd, yb, 1.5, beta, noalloc=True)
+        err = np.abs(ya.cpu().numpy().astype(np.float64) - orc.spmv_csr(R, x, 1.5, beta, y0))
+        assert (err <= tol * (1.5 * orc.absrow(R, x) + abs(beta * y0)) + 1e-30).all()
+        assert torch.equal(ya, yb)
