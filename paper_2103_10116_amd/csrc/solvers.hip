@@ -840,21 +840,25 @@ __global__ __launch_bounds__(RB) void k_gm_backsolve(KState* st) {
   if ((int)threadIdx.x < k) st->y[threadIdx.x] = gy[threadIdx.x];
 }
 
-// x += V(:, 0..k-1) y
+// x += V(:, 0..k-1) y.  The vectors are scaled first: y[i] * sc[i] grows with
+// ||r|| / ||A||^2, which can leave the range of FP64 where y and x are inside
+// it (A of about 2^-400, r of 2^300: y 2^700, sc 2^400).
 __global__ __launch_bounds__(RB) void k_gm_xupdate(int64_t n, int64_t ldv,
                                                    const double* __restrict__ V,
                                                    double* __restrict__ x, const KState* st) {
   if (st->done) return;
-  __shared__ double y[MAXM];
+  __shared__ double y[MAXM], sc[MAXM];
   const int k = st->k;
-  if (threadIdx.x < MAXM)
-    y[threadIdx.x] = (int)threadIdx.x < k ? st->y[threadIdx.x] * st->sc[threadIdx.x] : 0.0;
+  if (threadIdx.x < MAXM) {
+    y[threadIdx.x] = (int)threadIdx.x < k ? st->y[threadIdx.x] : 0.0;
+    sc[threadIdx.x] = (int)threadIdx.x < k ? st->sc[threadIdx.x] : 0.0;
+  }
   __syncthreads();
   GRID_STRIDE(r, n) {
     double xr = x[r];
 #pragma unroll
     for (int i = 0; i < MAXM; ++i)
-      if (i < k) xr += y[i] * V[i * ldv + r];
+      if (i < k) xr += y[i] * (sc[i] * V[i * ldv + r]);
     x[r] = xr;
   }
 }
