@@ -576,6 +576,7 @@ bool bins_fit(const mxs_ctx* ctx, int64_t n, int64_t ncols, int64_t nnz, int64_t
 mxs_status build_bins(mxs_ctx* ctx, mxs_matrix* A, BinPart& B, int64_t n, int64_t ncols,
                       int64_t nnz, const std::vector<int32_t>& rp, const int32_t* d_rp,
                       const int32_t* d_col, const void* d_val, mxs_dtype dt) {
+  A->copied = true;
   const size_t vb = value_bytes(dt), xb = dt == MXS_F64 ? 8 : 4;
   const int P = panel_count(ncols, xb, ctx->num_cus);
   const int W = (int)((ncols + P - 1) / P);

@@ -219,6 +219,9 @@ struct mxs_matrix {
   int64_t bytes = 0;
   // host copy of the row pointers (analysis data kept for conversions)
   std::vector<int32_t> h_rowptr;
+  // set-up: a second copy of the entries (diagonals, bins) was begun; there
+  // was no room for one
+  bool copied = false, plain = false;
 };
 
 // Jacobi: 1/a_ii per row; block Jacobi: inverted diagonal blocks,

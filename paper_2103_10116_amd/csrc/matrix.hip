@@ -621,6 +621,39 @@ mxs_matrix* new_matrix(mxs_ctx* ctx) {
   return A;
 }
 
+// Gives back the memory that A took after it owned `count` blocks of `bytes`.
+void release_after(mxs_matrix* A, size_t count, int64_t bytes) {
+  while (A->owned.size() > count) {
+    A->alloc.release(A->owned.back());
+    A->owned.pop_back();
+  }
+  A->bytes = bytes;
+}
+
+// Builds A's product with build(); where that stops for want of memory (or
+// beyond the index range of a layout) after a second copy of the entries was
+// begun, once more without one: such copies only make products faster.
+template <typename F>
+mxs_status build_with_room(mxs_ctx* ctx, mxs_matrix* A, F build) {
+  const size_t count = A->owned.size();
+  const int64_t bytes = A->bytes;
+  const CsrPart csr = A->csr;
+  const CooPart coo = A->coo;
+  const EllPart ell = A->ell;
+  const std::string error = ctx->last_error;
+  const mxs_status st = build();
+  if ((st != MXS_OOM && st != MXS_UNSUPPORTED) || !A->copied) return st;
+  (void)hipStreamSynchronize(ctx->stream);
+  release_after(A, count, bytes);
+  A->csr = csr;
+  A->coo = coo;
+  A->ell = ell;
+  A->plain = true;
+  A->copied = false;
+  ctx->last_error = error;
+  return build();
+}
+
 void free_matrix(mxs_matrix* A) {
   if (!A) return;
   (void)hipSetDevice(A->device);
@@ -838,8 +871,10 @@ mxs_status refresh_panel_values(mxs_ctx* ctx, mxs_matrix* A) {
 
 namespace {
 
-// nothing about the product's kernel was asked for
-bool no_kernel_asked(const mxs_convert_opts* o) {
+// nothing about the product's kernel was asked for, and there is room for a
+// second copy of the entries as far as is known
+bool copy_wanted(const mxs_matrix* A, const mxs_convert_opts* o) {
+  if (A->plain) return false;
   return !o || (o->csr_kernel == MXS_CSR_AUTO && o->coo_kernel == MXS_COO_AUTO &&
                 o->col_panels == 0 && o->block_nnz <= 0 && o->waves_per_group <= 0 &&
                 o->lanes_per_row <= 0 && o->rows_per_group <= 0);
@@ -857,7 +892,7 @@ mxs_status build_csr_merge(mxs_ctx* ctx, mxs_matrix* A, const mxs_convert_opts* 
   // 56.5 vs 58.0 us, s = 1.79 119.1 vs 119.5 us)
   A->csr.wpb = (opts && opts->waves_per_group > 1) ? 4 : 1;
   const int panels = merge_panels(A, opts);
-  if (no_kernel_asked(opts) && bins_fit(ctx, n, A->ncols, nnz, max_row, A->dt)) {
+  if (copy_wanted(A, opts) && bins_fit(ctx, n, A->ncols, nnz, max_row, A->dt)) {
     CsrPart& P = A->csr;
     P.merge = true;
     P.block_nnz = C;
@@ -919,6 +954,7 @@ mxs_status fill_diag(mxs_ctx* ctx, const DiagPart& P, int64_t n, const int32_t* 
 mxs_status build_diag(mxs_ctx* ctx, mxs_matrix* A, DiagPart& P, int64_t n, int64_t nnz,
                       int64_t max_row, const int32_t* rp, const int32_t* col, size_t vb) {
   if (max_row > kMaxDiags || nnz < kDiagMinEntries) return MXS_OK;
+  A->copied = true;
   constexpr size_t kTab = kTable * 8, kRow = kTable * 4, kOff = (kMaxMasks + 1) * 65 * 4;
   char* tmp = (char*)ctx->alloc.alloc(kTab + kRow + 8 + kOff + kTable);
   if (!tmp) return fail(ctx, MXS_OOM, "diagonals");
@@ -931,6 +967,8 @@ mxs_status build_diag(mxs_ctx* ctx, mxs_matrix* A, DiagPart& P, int64_t n, int64
   int32_t count = 0, bad = 0;
   const int64_t padded = (n + 63) / 64 * 64;
   const int g = grid_for(ctx, n, 256);
+  const size_t owned = A->owned.size();
+  const int64_t bytes = A->bytes;
   DiagPart Q;
   do {
     if (hipMemsetAsync(tmp, 0, kTab + kRow + 8, ctx->stream) != hipSuccess) {
@@ -983,6 +1021,7 @@ mxs_status build_diag(mxs_ctx* ctx, mxs_matrix* A, DiagPart& P, int64_t n, int64
     P = Q;
   } while (0);
   (void)hipStreamSynchronize(ctx->stream);
+  if (!P.on()) release_after(A, owned, bytes);
   ctx->alloc.release(tmp);
   return st;
 }
@@ -1027,11 +1066,12 @@ mxs_status build_csr_partition(mxs_ctx* ctx, mxs_matrix* A, int block_nnz,
     int64_t bad = 0;
     if (maxL > 64 && (A->dt == MXS_F64 || A->dt == MXS_F32 || A->dt == MXS_F16_ROWSCALED) &&
         (merge_panels(A, opts) > 1 ||
-         (no_kernel_asked(opts) && bins_fit(ctx, A->n, A->ncols, A->nnz, maxL, A->dt)) || merge_rows(rp, A->nnz, merge_chunk(opts), crow, &bad)))
+         (copy_wanted(A, opts) && bins_fit(ctx, A->n, A->ncols, A->nnz, maxL, A->dt)) ||
+         merge_rows(rp, A->nnz, merge_chunk(opts), crow, &bad)))
       kind_eff = MXS_CSR_MERGE;
   }
   if (kind_eff == MXS_CSR_MERGE) return build_csr_merge(ctx, A, opts, maxL);
-  if (no_kernel_asked(opts) && kind != MXS_CSR_MERGE &&
+  if (copy_wanted(A, opts) &&
       (A->dt == MXS_F64 || A->dt == MXS_F32 || A->dt == MXS_F16_ROWSCALED)) {
     CsrPart& P = A->csr;
     const size_t vb = value_bytes(A->dt);
@@ -1354,6 +1394,7 @@ mxs_status coo_bins(mxs_ctx* ctx, const mxs_matrix* S, mxs_matrix* A, int* d_err
   if (sizeof(V) == 8)
     return build_bins(ctx, A, A->coo.bin, S->n, S->ncols, S->nnz, S->h_rowptr, S->csr.rowptr,
                       S->csr.col, S->csr.val, A->dt);
+  A->copied = true;
   void* v = ctx->alloc.alloc((size_t)S->nnz * sizeof(V) + 16);
   if (!v) return fail(ctx, MXS_OOM, "row bins: values");
   mxs_status st = cast_into<V>(ctx, S->nnz, (const double*)S->csr.val, v, d_err);
@@ -1367,6 +1408,7 @@ mxs_status coo_bins(mxs_ctx* ctx, const mxs_matrix* S, mxs_matrix* A, int* d_err
 
 // the same for the hybrid's COO part (row-ordered in A->coo, values cast)
 mxs_status hyb_bins(mxs_ctx* ctx, mxs_matrix* A, const std::vector<int64_t>& off) {
+  A->copied = true;
   const int64_t n = A->n;
   std::vector<int32_t> rp((size_t)n + 1);
   for (int64_t i = 0; i <= n; ++i) rp[(size_t)i] = (int32_t)off[(size_t)i];
@@ -1421,7 +1463,7 @@ mxs_status convert_typed(mxs_ctx* ctx, const mxs_matrix* S, mxs_matrix* A, mxs_f
     const int req = opts ? opts->col_panels : 0;
     const int P = (req > 1 || (req == 0 && Kmax > 64)) ? merge_panels(A, opts) : 1;
     const bool bins =
-        no_kernel_asked(opts) && Kmax > 64 && bins_fit(ctx, n, S->ncols, nnz, Kmax, A->dt);
+        copy_wanted(A, opts) && Kmax > 64 && bins_fit(ctx, n, S->ncols, nnz, Kmax, A->dt);
     if (bins) {
       if (mxs_status st = coo_bins<V>(ctx, S, A, d_err)) return st;
     }
@@ -1438,7 +1480,7 @@ mxs_status convert_typed(mxs_ctx* ctx, const mxs_matrix* S, mxs_matrix* A, mxs_f
                                       ctx->stream));
     mxs_status st = cast_into<V>(ctx, nnz, (const double*)S->csr.val, A->coo.val, d_err);
     if (st) return st;
-    if (no_kernel_asked(opts)) {
+    if (copy_wanted(A, opts)) {
       CooPart& C = A->coo;
       if (mxs_status e = build_diag(ctx, A, C.diag, n, nnz, Kmax, rp, S->csr.col, vb)) return e;
       if (C.diag.on())
@@ -1497,7 +1539,7 @@ mxs_status convert_typed(mxs_ctx* ctx, const mxs_matrix* S, mxs_matrix* A, mxs_f
         d_err);
     MXS_HIP_TRY(ctx, hipGetLastError());
   }
-  if (K >= Kmax && K > 0 && no_kernel_asked(opts)) {
+  if (K >= Kmax && K > 0 && copy_wanted(A, opts)) {
     EllPart& P = A->ell;
     if (mxs_status st = build_diag(ctx, A, P.diag, n, nnz, Kmax, rp, S->csr.col, vb)) return st;
     if (P.diag.on())
@@ -1527,7 +1569,7 @@ mxs_status convert_typed(mxs_ctx* ctx, const mxs_matrix* S, mxs_matrix* A, mxs_f
   // the panel partials writes every row
   const int req = opts ? opts->col_panels : 0;
   const int P = (cnnz > 0 && (req > 1 || (req == 0 && Kmax > 64))) ? merge_panels(A, opts) : 1;
-  if (no_kernel_asked(opts) && Kmax > 64 && bins_fit(ctx, n, A->ncols, cnnz, Kmax - K, A->dt)) {
+  if (copy_wanted(A, opts) && Kmax > 64 && bins_fit(ctx, n, A->ncols, cnnz, Kmax - K, A->dt)) {
     // an ELL part of at most a quarter of the entries goes into the bins too:
     // its launch reads x at random once more and leaves y to be read back
     // (10^6 rows, s = 2.0, one slot a row, FP32: 34.3 us with it, 26.8 without).
@@ -1781,7 +1823,7 @@ mxs_status mxs::create_csr(mxs_ctx* ctx, int64_t nrows, int64_t ncols, int64_t n
       st = fail(ctx, MXS_HIP, "reading back the row pointers failed");
       break;
     }
-    st = build_csr_partition(ctx, A, 512);
+    st = build_with_room(ctx, A, [&] { return build_csr_partition(ctx, A, 512); });
   } while (0);
   if (st) {
     (void)hipStreamSynchronize(ctx->stream);
@@ -1890,9 +1932,11 @@ mxs_status mxs_matrix_convert(mxs_ctx* ctx, const mxs_matrix* src, mxs_format fm
       break;
     }
     if (dt == MXS_F64) {
-      st = convert_typed<double>(ctx, src, A, fmt, opts, d_err);
+      st = build_with_room(
+          ctx, A, [&] { return convert_typed<double>(ctx, src, A, fmt, opts, d_err); });
     } else if (dt == MXS_F32) {
-      st = convert_typed<float>(ctx, src, A, fmt, opts, d_err);
+      st = build_with_room(
+          ctx, A, [&] { return convert_typed<float>(ctx, src, A, fmt, opts, d_err); });
     } else {
       const int64_t n = src->n, nnz = src->nnz;
       A->csr.rowptr = (int32_t*)mat_alloc(A, (n + 1) * 4);
@@ -1915,7 +1959,9 @@ mxs_status mxs_matrix_convert(mxs_ctx* ctx, const mxs_matrix* src, mxs_format fm
             n, src->csr.rowptr, (const double*)src->csr.val, (uint16_t*)A->csr.val, A->csr.scale,
             d_err);
       A->h_rowptr = src->h_rowptr;
-      st = build_csr_partition(ctx, A, clamp_block_nnz(opts ? opts->block_nnz : 0), opts);
+      st = build_with_room(ctx, A, [&] {
+        return build_csr_partition(ctx, A, clamp_block_nnz(opts ? opts->block_nnz : 0), opts);
+      });
     }
     if (st) break;
     int err = 0;

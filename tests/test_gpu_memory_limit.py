@@ -1,0 +1,151 @@
+"""A caller's allocator that runs short.  The second copies of a matrix's
+entries (by diagonals, by row bins) only make products faster: where they do
+not fit, a matrix is still created and converted, in the memory that its
+ordinary kernel takes."""
+import numpy as np
+import pytest
+
+from paper_2103_10116_amd import inputs as I
+from paper_2103_10116_amd import mxs
+
+pytestmark = pytest.mark.gpu
+
+
+class Limited(mxs.TorchAllocator):
+    """Refuses a block that would take the live bytes past `limit`."""
+
+    def __init__(self):
+        super().__init__(0)
+        self.limit, self.used, self.peak, self.frees, self.refused = None, 0, 0, 0, 0
+
+    def _on_alloc(self, nbytes, stream, user):
+        if self.limit is not None and self.used + nbytes > self.limit:
+            self.refused += 1
+            return None
+        p = super()._on_alloc(nbytes, stream, user)
+        if p:
+            self.used += nbytes
+            self.peak = max(self.peak, self.used)
+        return p
+
+    def _on_free(self, ptr, stream, user):
+        if ptr in self.live:
+            self.used -= self.live[ptr].numel()
+            self.frees += 1
+        super()._on_free(ptr, stream, user)
+
+
+def _powerlaw():
+    A = I.random_spd(1 << 16, seed=31)
+    assert A.nnz >= 1 << 19 and A.row_lengths().max() > 64
+    return A
+
+
+def _panels():
+    """An x of 4.8 MB in FP64: the ordinary kernels cut it into column panels."""
+    n, g = 600000, I.rng(33)
+    L = np.tile([8, 10], n // 2)
+    L[:2] = 100, 0
+    rows = np.repeat(np.arange(n), L)
+    rp = np.zeros(n + 1, np.int64)
+    np.cumsum(L, out=rp[1:])
+    share = n // np.maximum(L, 1)[rows]
+    col = (np.arange(rp[-1]) - rp[rows]) * share + (g.random(len(rows)) * share).astype(np.int64)
+    return I.CSRMatrix(n, n, rp.astype(np.int32), col.astype(np.int32),
+                       g.uniform(-1, 1, len(col)))
+
+
+SYSTEMS = {"stencil": lambda: I.stencil27(32), "powerlaw": _powerlaw, "panels": _panels}
+# format, type and the options that ask for the kernel AUTO would take without
+# a second copy
+CASES = [("stencil", "csr", "f64", dict(csr_kernel="products")),
+         ("stencil", "csr", "f32", dict(csr_kernel="rows_lds")),
+         ("stencil", "csr", "f16", dict(csr_kernel="rows_lds")),
+         ("stencil", "coo", "f64", dict(coo_kernel="lds")),
+         ("stencil", "ell", "f32", dict(coo_kernel="lds")),
+         ("stencil", "hyb", "f64", dict(coo_kernel="lds", ell_width=27)),
+         ("powerlaw", "csr", "f64", dict(csr_kernel="merge")),
+         ("powerlaw", "csr", "f32", dict(csr_kernel="merge")),
+         ("powerlaw", "csr", "f16", dict(csr_kernel="merge")),
+         ("powerlaw", "coo", "f64", dict(coo_kernel="lds")),
+         ("powerlaw", "coo", "f32", dict(coo_kernel="lds")),
+         ("powerlaw", "hyb", "f64", dict(coo_kernel="lds", ell_width=1)),
+         ("powerlaw", "hyb", "f32", dict(coo_kernel="lds", ell_width=4)),
+         ("panels", "csr", "f64", dict(csr_kernel="merge")),
+         ("panels", "coo", "f64", dict(coo_kernel="lds")),
+         ("panels", "hyb", "f64", dict(coo_kernel="lds", ell_width=1))]
+
+
+def _check(orc, torch, ctx, A, B, fmt, dt, beta=-0.5):
+    """One product against the oracle."""
+    x, y0, val = I.uniform_vector(A.n, 12), I.uniform_vector(A.n, 13), A.val
+    if dt != "f64":
+        x, y0, val = (v.astype(np.float32).astype(np.float64) for v in (x, y0, val))
+    if dt == "f16":
+        _, h, s = orc.rowscale_f16(A)
+        val = orc.f16_bits_to_f64(h) * np.repeat(s.astype(np.float64), A.row_lengths())
+    tdt = torch.float64 if dt == "f64" else torch.float32
+    R = I.CSRMatrix(A.n, A.ncols, A.rowptr, A.col, val)
+    y = torch.from_numpy(y0).to(tdt).cuda()
+    mxs.spmv(ctx, B, torch.from_numpy(x).to(tdt).cuda(), y, 1.5, beta)
+    err = np.abs(y.cpu().numpy().astype(np.float64) - orc.spmv_csr(R, x, 1.5, beta, y0))
+    tol = 1e-13 if dt == "f64" else 1e-5
+    assert (err <= tol * (1.5 * orc.absrow(R, x) + abs(beta * y0)) + 1e-30).all(), (fmt, dt)
+
+
+# (CSR in column panels takes more memory than in bins)
+@pytest.mark.parametrize("system,fmt,dt,plain", [c for c in CASES if c[:2] != ("panels", "csr")])
+def test_conversion_without_room_for_a_second_copy(orc, system, fmt, dt, plain):
+    import torch
+    A = SYSTEMS[system]()
+    al = Limited()
+    ctx = mxs.Context(0, allocator=al)
+    M = mxs.Matrix.from_host(ctx, A)
+    _check(orc, torch, ctx, A, M, "csr", "f64")     # grows the context's own scratch
+    al.peak = base = al.used
+    with_width = {k: v for k, v in plain.items() if k == "ell_width"}
+    P = M.convert(fmt, dt, **plain)
+    need, kept = al.peak - base, P.info()["bytes"]
+    P.close()
+    assert al.used == base
+    full = M.convert(fmt, dt, **with_width)
+    assert full.info()["bytes"] > kept
+    full.close()
+    al.limit = base + need
+    B = M.convert(fmt, dt, **with_width)
+    assert al.refused and B.info()["bytes"] == kept and al.used - base == kept
+    al.limit = None
+    _check(orc, torch, ctx, A, B, fmt, dt)
+    B.close()
+    # still an error where the matrix itself does not fit
+    base = al.used
+    al.limit = base + kept // 2
+    with pytest.raises(mxs.MxsError) as e:
+        M.convert(fmt, dt, **with_width)
+    assert e.value.status == mxs.OOM and al.used == base
+    M.close()
+    ctx.close()
+    assert not al.live
+
+
+@pytest.mark.parametrize("system", ["stencil", "powerlaw"])
+def test_creation_without_room_for_a_second_copy(orc, system):
+    import torch
+    A = SYSTEMS[system]()
+    al = Limited()
+    ctx = mxs.Context(0, allocator=al)
+    # rowptr, col and val, the kernel's tables (a few bytes a row)
+    al.limit = 12 * A.nnz + 16 * A.n + 100000
+    M = mxs.Matrix.from_host(ctx, A)
+    assert al.refused
+    al.limit = None
+    _check(orc, torch, ctx, A, M, "csr", "f64")
+    # a source without a copy makes conversions with one
+    P, B = M.convert("coo", "f64", coo_kernel="lds"), M.convert("coo", "f64")
+    assert B.info()["bytes"] > P.info()["bytes"]
+    P.close()
+    _check(orc, torch, ctx, A, B, "coo", "f64")
+    B.close()
+    M.close()
+    ctx.close()
+    assert not al.live

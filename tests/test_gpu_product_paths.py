@@ -1,0 +1,167 @@
+"""Which product a matrix takes where two rules meet, and the products inside
+solvers that no other test reaches: the two passes near their largest number of
+column panels, the FP32 and row-scaled FP16 dot products of both new forms in
+refinement's inner solves, preconditioned CG's p.q from the bins, and more bins
+than dot partials."""
+import numpy as np
+import pytest
+
+from paper_2103_10116_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    from paper_2103_10116_amd import mxs
+    ctx = mxs.Context(0)
+    yield mxs, ctx, torch
+    ctx.close()
+
+
+def _shared_columns(ncols, lens, seed):
+    """Rows of the given lengths, one column drawn from each equal share."""
+    g = I.rng(seed)
+    lens = np.asarray(lens, np.int64)
+    rp = np.zeros(len(lens) + 1, np.int64)
+    np.cumsum(lens, out=rp[1:])
+    rows = np.repeat(np.arange(len(lens)), lens)
+    L = lens[rows]
+    j = np.arange(rp[-1]) - rp[rows]
+    lo, hi = j * ncols // L, (j + 1) * ncols // L
+    col = lo + (g.random(len(lo)) * (hi - lo)).astype(np.int64)
+    return I.CSRMatrix(len(lens), ncols, rp.astype(np.int32), col.astype(np.int32),
+                       g.uniform(-1, 1, len(col)))
+
+
+# columns on either side of 128 panels (20448 FP64 or 32768 FP32 columns each),
+# at 147 of them and on either side of 160, the most that the two passes take
+PANELS = [("f64", 128 * 20448, True), ("f64", 128 * 20448 + 1, True), ("f64", 3000001, True),
+          ("f64", 160 * 20448, True), ("f64", 160 * 20448 + 1, False),
+          ("f32", 128 * 32768 + 1, True), ("f32", 160 * 32768, True),
+          ("f32", 160 * 32768 + 1, False), ("f16", 4800001, True)]
+
+
+@pytest.mark.parametrize("dt,ncols,takes", PANELS)
+def test_most_panels(env, orc, dt, ncols, takes):
+    """The path itself: a matrix whose kernel is asked for keeps the arrays of
+    the column panels, so AUTO's bytes are the same exactly when it falls back
+    on them."""
+    mxs, ctx, torch = env
+    A = _shared_columns(ncols, [30] * 20000 + [100], 11)
+    M = mxs.Matrix.from_host(ctx, A)
+    B, P = M.convert("csr", dt), M.convert("csr", dt, csr_kernel="merge")
+    assert (B.info()["bytes"] != P.info()["bytes"]) == takes
+    x, y0, val = I.uniform_vector(ncols, 12), I.uniform_vector(A.n, 13), A.val
+    if dt != "f64":
+        x, y0, val = (v.astype(np.float32).astype(np.float64) for v in (x, y0, val))
+    if dt == "f16":
+        _, h, s = orc.rowscale_f16(A)
+        val = orc.f16_bits_to_f64(h) * np.repeat(s.astype(np.float64), A.row_lengths())
+    R = I.CSRMatrix(A.n, ncols, A.rowptr, A.col, val)
+    tdt = torch.float64 if dt == "f64" else torch.float32
+    ya = torch.from_numpy(y0).to(tdt).cuda()
+    yb = ya.clone()
+    xd = torch.from_numpy(x).to(tdt).cuda()
+    mxs.spmv(ctx, B, xd, ya, 1.5, -0.5)
+    mxs.spmv(ctx, B, xd, yb, 1.5, -0.5, noalloc=True)
+    err = np.abs(ya.cpu().numpy().astype(np.float64) - orc.spmv_csr(R, x, 1.5, -0.5, y0))
+    tol = 1e-13 if dt == "f64" else 1e-5
+    assert (err <= tol * (1.5 * orc.absrow(R, x) + 0.5 * np.abs(y0)) + 1e-30).all()
+    assert torch.equal(ya, yb)
+    for m in (B, P, M):
+        m.close()
+
+
+def _slack(orc, A, b, x):
+    """Rounding of the residual's own evaluation."""
+    return 64 * 2.0 ** -53 * np.linalg.norm(np.abs(b) + orc.absrow(A, x)) / np.linalg.norm(b)
+
+
+def _spd():
+    A = I.random_spd(1 << 16, seed=31)
+    rows = np.repeat(np.arange(A.n), A.row_lengths())
+    A.val[rows == A.col] *= 4.0
+    return A
+
+
+@pytest.mark.parametrize("carry", [False, True])
+@pytest.mark.parametrize("precond", [None, "jacobi", "block_jacobi"])
+@pytest.mark.parametrize("low", ["f32", "f16"])
+@pytest.mark.parametrize("system", ["grid", "powerlaw"])
+def test_refinement_inner_products(env, orc, system, low, precond, carry):
+    """The inner CG's p.q from FP32 and row-scaled FP16 products over diagonals
+    (31^3: a last work-group and slice that are not full) and over bins."""
+    mxs, ctx, torch = env
+    A = I.poisson3d(31) if system == "grid" else _spd()
+    b = I.uniform_vector(A.n, 61)
+    M = mxs.Matrix.from_host(ctx, A)
+    L = M.convert("csr", low)
+    kept = M.convert("csr", low, csr_kernel="rows_lds" if system == "grid" else "merge")
+    assert L.info()["bytes"] > kept.info()["bytes"]        # the second copy
+    P = mxs.Precond(ctx, M, precond, 4) if precond else None
+    x = torch.zeros(A.n, dtype=torch.float64, device="cuda")
+    r = mxs.solve_ir(ctx, M, L, torch.from_numpy(b).cuda(), x, tol=1e-10, precond=P,
+                     carry_direction=carry)
+    xh = x.cpu().numpy()
+    assert r.status == mxs.OK
+    assert orc.true_relres(A, b, xh) <= 1e-10 + _slack(orc, A, b, xh)
+    # the same steps as with the products that form no dots of this kind
+    x2 = torch.zeros_like(x)
+    r2 = mxs.solve_ir(ctx, M, kept, torch.from_numpy(b).cuda(), x2, tol=1e-10, precond=P,
+                      carry_direction=carry)
+    assert abs(r.outer_iters - r2.outer_iters) <= 1
+    assert abs(r.inner_iters_total - r2.inner_iters_total) <= 0.1 * r2.inner_iters_total + 2
+
+
+@pytest.mark.parametrize("kind,bs", [("jacobi", 1), ("block_jacobi", 8)])
+@pytest.mark.parametrize("system", ["grid", "powerlaw"])
+def test_preconditioned_cg_products(env, orc, system, kind, bs):
+    mxs, ctx, torch = env
+    A = I.poisson3d(31) if system == "grid" else _spd()
+    b = I.uniform_vector(A.n, 62)
+    M = mxs.Matrix.from_host(ctx, A)
+    P = mxs.Precond(ctx, M, kind, bs)
+    x = torch.zeros(A.n, dtype=torch.float64, device="cuda")
+    r = mxs.solve(ctx, "cg", M, torch.from_numpy(b).cuda(), x, tol=1e-10, precond=P)
+    xh = x.cpu().numpy()
+    assert orc.true_relres(A, b, xh) <= 1e-10 + _slack(orc, A, b, xh)
+    ref = orc.pcg(A, b, orc.jacobi(A)[1] if kind == "jacobi" else orc.block_jacobi(A, bs)[1],
+                  tol=1e-10)
+    assert abs(r.iters - ref.iters) <= max(3, ref.iters // 10)
+
+
+@pytest.mark.parametrize("solver", ["cg", "bicgstab"])
+def test_more_bins_than_dot_partials(env, orc, solver):
+    """2^21 rows whose 11 entries lie in 11 panels, so that a bin of 4096
+    partial sums holds 372 rows: 5600 bins, beyond the 4096 dot partials; the
+    solvers form their dots apart from the product."""
+    mxs, ctx, torch = env
+    n = 1 << 21
+    g = I.rng(71)
+    # circulant edges at five distances, and row 0 joined to 100 others
+    far = (np.array([1, 2, 3, 4, 5]) * (n // 11) + g.integers(0, 1000, 5)).astype(np.int64)
+    i = np.arange(n, dtype=np.int64)
+    rows = np.concatenate([np.tile(i, 5), np.zeros(100, np.int64)])
+    cols = np.concatenate([(i + d) % n for d in far] + [np.arange(1, 101) * 20001])
+    assert not np.isin(cols[-100:], np.concatenate([far, (n - far) % n])).any()
+    w = g.uniform(-1, 1, len(rows))
+    r, c = np.concatenate([rows, cols, i]), np.concatenate([cols, rows, i])
+    v = np.concatenate([w, w, np.where(i == 0, 150.0, 14.0)])
+    order = np.lexsort((c, r))
+    r, c, v = r[order], c[order], v[order]
+    rp = np.zeros(n + 1, np.int64)
+    np.cumsum(np.bincount(r, minlength=n), out=rp[1:])
+    A = I.CSRMatrix(n, n, rp.astype(np.int32), c.astype(np.int32), v)
+    assert A.row_lengths().max() > 64
+    M = mxs.Matrix.from_host(ctx, A)
+    P = M.convert("csr", "f64", csr_kernel="merge")
+    assert M.info()["bytes"] != P.info()["bytes"]          # the two passes
+    P.close()
+    b = I.uniform_vector(n, 72)
+    x = torch.zeros(n, dtype=torch.float64, device="cuda")
+    mxs.solve(ctx, solver, M, torch.from_numpy(b).cuda(), x, tol=1e-10)
+    xh = x.cpu().numpy()
+    assert orc.true_relres(A, b, xh) <= 1e-10 + _slack(orc, A, b, xh)
+    M.close()
