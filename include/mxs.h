@@ -21,8 +21,9 @@
  *  - A ctx must not be used by two host threads at the same time.  A
  *    matrix is read-only during a product or a solve: the chunked products
  *    (merge-path CSR, COO, the COO part of hybrid) keep their per-chunk
- *    continuation partials in scratch memory of the ctx, so one matrix may
- *    be used by several ctxs on different streams at once.
+ *    continuation partials, and the two-pass product its partial sums, in
+ *    scratch memory of the ctx, so one matrix may be used by several ctxs on
+ *    different streams at once.
  */
 #ifndef MXS_H
 #define MXS_H
@@ -271,16 +272,22 @@ mxs_status mxs_matrix_destroy(mxs_matrix* A);
  * than the Infinity Cache) read those arrays with non-temporal loads, so
  * they do not displace x, y and the dirty lines of y from the caches;
  * smaller matrices keep ordinary loads, which leave them cached for the
- * next product. */
+ * next product.
+ * The ctx's scratch grows at the first product that needs more.  The two-pass
+ * product's is up to 8 (FP64) or 4 bytes an entry and a quarter more; where
+ * that cannot be allocated, this and the ctx's later products of such
+ * matrices run by the ordinary kernel instead (CSR: a wave per row). */
 mxs_status mxs_spmv(mxs_ctx* ctx, const void* alpha, const mxs_matrix* A, const void* x,
                     const void* beta, void* y);
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * product as mxs_spmv, same arguments, same kernels and the same result bit
- * for bit, but it never allocates or frees memory.  The scratch that the
+ * for bit (except where mxs_spmv had no memory for the two-pass product's
+ * scratch), but it never allocates or frees memory.  The scratch that the
  * chunked kernels need (merge-path CSR, COO and the COO part of hybrid keep
- * one row index and one partial sum per chunk) comes from a fixed device
+ * one row index and one partial sum per chunk; the two-pass product takes as
+ * many batches of rows as its partial sums ask for) comes from a fixed device
  * array of MXS_NOALLOC_SCRATCH_BYTES (64 MiB) in each GPU's copy of the
  * library, set up by mxs_ctx_create and held until the process ends.  A
  * product needing more scratch than that returns MXS_UNSUPPORTED before

@@ -672,6 +672,9 @@ mxs_status build_bins(mxs_ctx* ctx, mxs_matrix* A, BinPart& B, int64_t n, int64_
         B.batch.push_back((int32_t)b);
     B.batch.push_back((int32_t)nb);
     const size_t nbatch = B.batch.size() - 1;
+    for (size_t q = 0; q < nbatch; ++q)
+      B.least = std::max<int64_t>(B.least, bpart[(size_t)B.batch[q + 1]] -
+                                               bpart[(size_t)B.batch[q]]);
     // pass 1's order: panel, batch, bin, each panel's share of a batch a whole
     // number of chunks; work lists of about equal shares, one work-group per
     // CU in all: list 0 takes all batches, the others one each
@@ -777,10 +780,6 @@ mxs_status refresh_bins(mxs_ctx* ctx, BinPart& B, const int32_t* d_rp, const int
   layout(ctx, B, 2, d_rp, d_col, val, vb);
   MXS_HIP_TRY(ctx, hipGetLastError());
   return MXS_OK;
-}
-
-size_t bins_scratch_bytes(const BinPart& B, mxs_dtype dt) {
-  return (size_t)B.parts * (dt == MXS_F64 ? 8 : 4);
 }
 
 namespace {

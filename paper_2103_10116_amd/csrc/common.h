@@ -52,8 +52,12 @@ struct mxs_ctx {
   int num_cus = 256;
   // grow-only scratch for solvers and format conversion
   mxs::Workspace ws;
-  // grow-only scratch of the chunked products (continuation partials)
+  // grow-only scratch of the chunked products (continuation partials) and of
+  // the two-pass product (partial sums); the least size that the allocator
+  // has refused is not asked for again (a failing call per product would cost
+  // more than the ordinary kernel, and cannot be made under capture)
   mxs::Workspace spmv_ws;
+  size_t spmv_refused = SIZE_MAX;
   // pinned host mirror of small device state blocks
   void* pinned = nullptr;
   size_t pinned_bytes = 0;
@@ -89,6 +93,7 @@ struct BinPart {
   int4* work = nullptr;
   std::vector<int32_t> work_at, batch, batch_base;
   int64_t nbins = 0, parts = 0, ncols = 0;
+  int64_t least = 0;  // partial sums of the largest batch
   int panels = 0, width = 0;
   bool on() const { return nbins > 0; }
 };
@@ -266,12 +271,6 @@ inline size_t value_bytes(mxs_dtype dt) {
 // returns at once (solvers queue iterations past convergence this way)
 mxs_status launch_spmv(mxs_ctx* ctx, const mxs_matrix* A, const void* alpha, const void* x,
                        const void* beta, void* y, const int32_t* skip);
-// Device scratch one product of A needs (continuation partials of the
-// merge-path CSR and COO chunks; 0 for the other kernels), and the same
-// product with that scratch supplied by the caller (at least
-// spmv_scratch_bytes(A) bytes, 256-byte aligned, not in use by any other
-// product until this one completes on ctx->stream).
-size_t spmv_scratch_bytes(const mxs_matrix* A);
 // y = A x (square A) and, in the same launches, work-group partial sums of
 // w[i] * y[i] in dpart (w = x when NULL: CG's p.q with x = p), and with
 // nv = 2 also of y[i]^2, interleaved (dpart[b * nv + v]): returns how many
@@ -288,12 +287,16 @@ int launch_spmv_dot(mxs_ctx* ctx, const mxs_matrix* A, const void* x, void* y,
 constexpr size_t kNoAllocScratchBytes = size_t(64) << 20;
 mxs_status noalloc_scratch_init(mxs_ctx* ctx);
 void* noalloc_scratch(int device);
+// The product with `bytes` of device scratch supplied by the caller (256-byte
+// aligned, not in use by any other product until this one completes on
+// ctx->stream): at least what A's chunks or bins need, but less than a CSR
+// matrix's bins need is possible.
 mxs_status launch_spmv_scratch(mxs_ctx* ctx, const mxs_matrix* A, const void* alpha,
                                const void* x, const void* beta, void* y, const int32_t* skip,
                                void* scratch, size_t bytes);
 // The two-pass product (binned.hip): whether a matrix takes it, its set-up
 // from row-ordered entries (rp: host copy of the row pointers d_rp), its
-// scratch and its launch (prod: prod_bytes of scratch, at least a batch's;
+// launch (prod: prod_bytes of scratch, at least the largest batch's;
 // nv > 0: dot partials per bin as in launch_spmv_dot).
 bool bins_fit(const mxs_ctx* ctx, int64_t n, int64_t ncols, int64_t nnz, int64_t max_row,
               mxs_dtype dt);
@@ -302,7 +305,11 @@ mxs_status build_bins(mxs_ctx* ctx, mxs_matrix* A, BinPart& B, int64_t n, int64_
                       const int32_t* d_col, const void* d_val, mxs_dtype dt);
 mxs_status refresh_bins(mxs_ctx* ctx, BinPart& B, const int32_t* d_rp, const int32_t* d_col,
                         const void* val, size_t vb);
-size_t bins_scratch_bytes(const BinPart& B, mxs_dtype dt);
+// whether `bytes` of scratch hold its largest batch (products run by the
+// ordinary kernel where they do not)
+inline bool bins_run(const BinPart& B, size_t xb, size_t bytes) {
+  return B.on() && (size_t)B.least * xb <= bytes;
+}
 void launch_bins(mxs_ctx* ctx, const BinPart& B, mxs_dtype dt, const float* scale,
                  const void* alpha, const void* x, const void* beta, void* y,
                  const int32_t* skip, void* prod, size_t prod_bytes, double* dpart = nullptr,

@@ -1,7 +1,7 @@
 """A caller's allocator that runs short.  The second copies of a matrix's
-entries (by diagonals, by row bins) only make products faster: where they do
-not fit, a matrix is still created and converted, in the memory that its
-ordinary kernel takes."""
+entries (by diagonals, by row bins) and the scratch of the two-pass product
+only make products faster: where they do not fit, a matrix is still created,
+converted and multiplied, in the memory that its ordinary kernel takes."""
 import numpy as np
 import pytest
 
@@ -147,5 +147,62 @@ def test_creation_without_room_for_a_second_copy(orc, system):
     _check(orc, torch, ctx, A, B, "coo", "f64")
     B.close()
     M.close()
+    ctx.close()
+    assert not al.live
+
+
+@pytest.mark.parametrize("beta", [0.0, -0.5])
+@pytest.mark.parametrize("system,fmt,dt,plain", [c for c in CASES if c[0] != "stencil"])
+def test_product_without_room_for_its_partial_sums(orc, system, fmt, dt, plain, beta):
+    import torch
+    A = SYSTEMS[system]()
+    al = Limited()
+    ctx = mxs.Context(0, allocator=al)
+    M = mxs.Matrix.from_host(ctx, A)
+    with_width = {k: v for k, v in plain.items() if k == "ell_width"}
+    P = M.convert(fmt, dt, **plain)
+    before = al.used
+    _check(orc, torch, ctx, A, P, fmt, dt, beta)
+    scratch = al.used - before                      # what the ordinary kernel takes
+    P.close()
+    ctx.close()
+    M.close()
+    al = Limited()
+    ctx = mxs.Context(0, allocator=al)
+    M = mxs.Matrix.from_host(ctx, A)
+    B = M.convert(fmt, dt, **with_width)
+    al.limit = al.used + scratch
+    _check(orc, torch, ctx, A, B, fmt, dt, beta)
+    assert al.refused
+    al.limit = None                                 # room again: the two passes again
+    _check(orc, torch, ctx, A, B, fmt, dt, beta)
+    B.close()
+    M.close()
+    ctx.close()
+    assert not al.live
+
+
+def test_solve_without_room_for_partial_sums(orc):
+    """CG's products by the ordinary kernel, p.q in a pass of its own."""
+    import torch
+    A = _powerlaw()
+    rows = np.repeat(np.arange(A.n), A.row_lengths())
+    A.val[rows == A.col] *= 4.0
+    b = I.uniform_vector(A.n, 32)
+    al = Limited()
+    ctx = mxs.Context(0, allocator=al)
+    small = mxs.Matrix.from_host(ctx, I.poisson3d(41))     # 68921 rows: the solver's vectors
+    xs = torch.zeros(41 ** 3, dtype=torch.float64, device="cuda")
+    mxs.solve(ctx, "cg", small, torch.ones_like(xs), xs, tol=1e-6)
+    M = mxs.Matrix.from_host(ctx, A)
+    al.limit = al.used + 64 * 1024
+    x = torch.zeros(A.n, dtype=torch.float64, device="cuda")
+    mxs.solve(ctx, "cg", M, torch.from_numpy(b).cuda(), x, tol=1e-10)
+    assert al.refused
+    xh = x.cpu().numpy()
+    slack = 64 * 2.0 ** -53 * np.linalg.norm(np.abs(b) + orc.absrow(A, xh)) / np.linalg.norm(b)
+    assert orc.true_relres(A, b, xh) <= 1e-10 + slack
+    M.close()
+    small.close()
     ctx.close()
     assert not al.live
