@@ -178,9 +178,11 @@ typedef struct {
                               When nothing about the kernel is asked for (csr_kernel, coo_kernel,
                               col_panels, block_nnz, waves_per_group, lanes_per_row and
                               rows_per_group all 0), a row has more than 64 entries and there are
-                              at least 2^19 entries over at least 32768 columns (CSR, COO, and the
-                              COO part of HYB), the product runs in two streaming passes over a
-                              second copy of the entries instead; info and exports are as above.
+                              at least 2^19 entries over 32768 to 3271680 (FP64) or 5242880 columns
+                              (CSR, COO, and the COO part of HYB; no row beyond some 30000 entries),
+                              the product runs in two streaming passes over a second copy of the
+                              entries instead (10 to 16 bytes an entry); info and exports are as
+                              above.
                               In the same way matrices of at least 2^17 entries on at most 64
                               diagonals (rows of at most 64 entries, at most 255 different sets of
                               diagonals, at most a fifth of them holes) run, in any format, over a

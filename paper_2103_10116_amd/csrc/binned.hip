@@ -61,15 +61,16 @@ constexpr int kMinPanels = 32;
 constexpr int kMaxPanels = 160;
 constexpr uint16_t kTopBit = 0x8000;
 
-// Panels of equal width whose slices fit LDS, as many as keep whole rounds
-// of one work-group per CU.  At least kMinPanels: a work-group loads its whole
+// Panels of equal width whose slices fit LDS, as many as share the CUs out
+// evenly where a panel gets two or more work-groups; above num_cus / 2 panels
+// the fewest that fit.  At least kMinPanels: a work-group loads its whole
 // slice, which on a short x would cost more than its entries (2^18 columns,
 // s = 1.79: FP64 27.8 us with 13 panels, 20.5 with 32, 22.6 with 128).
 int panel_count(int64_t ncols, size_t xb, int num_cus) {
   const int64_t w = xb == 8 ? kSlice<double> : kSlice<float>;
   const int64_t least = std::max<int64_t>(kMinPanels, (ncols + w - 1) / w);
   const int64_t share = num_cus / least;  // work-groups per panel
-  return (int)(share > 0 ? std::max<int64_t>(least, num_cus / share) : least);
+  return (int)(share > 1 ? std::max<int64_t>(least, num_cus / share) : least);
 }
 
 // most partial sums a row of L entries in at most P panels can make: one per
@@ -560,12 +561,19 @@ void layout(mxs_ctx* ctx, const BinPart& B, int write, const int32_t* d_rp,
 // 0.3M entries 10.7 -> 9.9 / 10.3 -> 9.3) and the set-up costs more than it
 // saves.  2^20 rows on 16384 columns, whose x the L1 still serves: 49.9 ->
 // 53.3 / 33.3 -> 36.9 with 8 entries a row; on 32768: 52.7 -> 53.2 /
-// 39.9 -> 37.8.  Also banded rows (24 entries within 20000 columns of the
-// diagonal): 152 -> 88 / 116 -> 58.  More than 160 panels would leave tiles
-// of little more than padding, and a row has to fit a bin.
+// 39.9 -> 37.8, even in FP64 there.  Also banded rows (24 entries within 20000
+// columns of the diagonal, with one long row): 152 -> 88 / 116 -> 58.  The
+// callers ask for a row of more than 64 entries besides: shorter rows gain too
+// where their columns are scattered, but their set-up, several times that of
+// the kernels over row blocks, has not been weighed.  At most kMaxPanels = 160
+// panels (3271680 FP64 columns, 5242880 others): with 8 entries a row scattered
+// over the columns 2617345 columns (129 panels) take 246 -> 201 / 182 -> 98
+// (81 panels), 3271680 (160) 335 -> 269, in FP32 4194305 (129) 290 -> 236 and
+// 5242880 (160) 360 -> 337, so more would gain nothing; and a row has to fit a
+// bin.
 bool bins_fit(const mxs_ctx* ctx, int64_t n, int64_t ncols, int64_t nnz, int64_t max_row,
               mxs_dtype dt) {
-    constexpr int64_t kMinCols = 32768, kMinEntries = int64_t(1) << 19;
+  constexpr int64_t kMinCols = 32768, kMinEntries = int64_t(1) << 19;
   if (dt != MXS_F64 && dt != MXS_F32 && dt != MXS_F16_ROWSCALED) return false;
   const size_t xb = dt == MXS_F64 ? 8 : 4;
   if (ncols < kMinCols || nnz < kMinEntries || nnz > INT32_MAX / 2) return false;
