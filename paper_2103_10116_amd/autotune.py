@@ -2,16 +2,19 @@
 
 * Batched CG: for each size class, the threads per system (128 ... 1024)
   that solves a batch of systems of that class fastest.
-* SpMV: for a CSR matrix, the kernel (row-block stream, lanes-per-row
-  vector, thread per row, rows from LDS or products through LDS) and its
-  work-unit shape with the shortest product.
+* SpMV: for a CSR or COO matrix, the kernel (for CSR row-block stream,
+  lanes-per-row vector, thread per row, rows from LDS or products through
+  LDS) and its work-unit shape with the shortest product; "auto" among
+  them, which alone can take a product over diagonals or in two passes.
 
-Results are cached as JSON keyed by the device name and the problem
-signature, so a configuration depends only on the inputs' sizes, never on
+Results are cached as JSON keyed by the device name, the problem signature,
+the candidates and the library's build, so a configuration depends only on the inputs' sizes, never on
 what else is running (the batched results stay bitwise reproducible).
 """
 from __future__ import annotations
 
+import functools
+import hashlib
 import json
 import os
 import time
@@ -46,11 +49,24 @@ def _device_name():
     return torch.cuda.get_device_name(0)
 
 
+@functools.lru_cache(maxsize=None)
+def _library():
+    from . import mxs
+    with open(mxs.LIB_PATH, "rb") as f:
+        return hashlib.sha256(f.read()).hexdigest()
+
+
+def _choices(candidates):
+    """What a cached choice was made among: the candidates and the kernels."""
+    text = json.dumps(candidates, sort_keys=True) + _library()
+    return hashlib.sha256(text.encode()).hexdigest()[:12]
+
+
 def tune_batch_classes(ctx, bounds=CLASS_BOUNDS, per_class=128, tol=1e-10, cache=DEFAULT_CACHE,
                        refresh=False, log=None):
     """Returns [(max_n, block, 0), ...] for mxs.Batch(classes=...)."""
     from . import mxs
-    key = f"batch|{_device_name()}|{','.join(map(str, bounds))}|{per_class}"
+    key = f"batch|{_device_name()}|{','.join(map(str, bounds))}|{per_class}|{_choices(BLOCKS)}"
     data = _load(cache)
     if not refresh and key in data:
         return [tuple(c) for c in data[key]["classes"]]
@@ -104,8 +120,9 @@ CSR_CANDIDATES = ([dict(csr_kernel="auto")] +
                   [dict(csr_kernel="products", block_nnz=b) for b in (512, 1024)] +
                   [dict(csr_kernel="merge", block_nnz=b) for b in (256, 512)])
 
-COO_CANDIDATES = [dict(coo_kernel=k, block_nnz=b, waves_per_group=w)
-                  for k in ("lds", "runs") for b in (256, 512, 1024) for w in (1, 4)]
+COO_CANDIDATES = ([dict(coo_kernel="auto")] +
+                  [dict(coo_kernel=k, block_nnz=b, waves_per_group=w)
+                   for k in ("lds", "runs") for b in (256, 512, 1024) for w in (1, 4)])
 CANDIDATES = {"csr": CSR_CANDIDATES, "coo": COO_CANDIDATES}
 
 
@@ -118,7 +135,8 @@ def tune_spmv(ctx, M, dtype="f64", reps=20, cache=DEFAULT_CACHE, signature=None,
     from . import mxs
     d = M.info()
     sig = signature or f"{d['nrows']}x{d['ncols']}:{d['nnz']}"
-    key = f"spmv|{_device_name()}|{sig}|{dtype}" + ("" if fmt == "csr" else f"|{fmt}")
+    key = (f"spmv|{_device_name()}|{sig}|{dtype}|{_choices(CANDIDATES[fmt])}" +
+           ("" if fmt == "csr" else f"|{fmt}"))
     data = _load(cache)
     if not refresh and key in data:
         return data[key]["opts"]
@@ -126,7 +144,7 @@ def tune_spmv(ctx, M, dtype="f64", reps=20, cache=DEFAULT_CACHE, signature=None,
     x = torch.rand(d["ncols"], dtype=tdt, device="cuda")
     y = torch.zeros(d["nrows"], dtype=tdt, device="cuda")
     best = None
-    timings = {}
+    timings, forms = {}, []
     for opts in CANDIDATES[fmt]:
         B = M.convert(fmt, dtype, **opts)
         for _ in range(3):
@@ -139,13 +157,19 @@ def tune_spmv(ctx, M, dtype="f64", reps=20, cache=DEFAULT_CACHE, signature=None,
         e1.record()
         e1.synchronize()
         t = e0.elapsed_time(e1) / reps
+        form = B.info()
+        forms.append((opts, form))
         B.close()
         name = json.dumps(opts, sort_keys=True)
         timings[name] = t
         if log:
             log(f"autotune spmv {sig} {dtype} {name}: {t*1e3:.1f} us")
         if best is None or t < best[1]:
-            best = (opts, t)
+            best = (opts, t, form)
+    if best[0] == {f"{fmt}_kernel": "auto"}:
+        # "auto", where it is a named candidate's product, goes by that name
+        named = [o for o, f in forms if f == best[2] and o != best[0]]
+        best = (named[0] if named else best[0], *best[1:])
     data[key] = {"opts": best[0], "ms": best[1], "timings_ms": timings}
     _save(cache, data)
     return best[0]

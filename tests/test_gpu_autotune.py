@@ -84,3 +84,54 @@ def test_tune_batch_classes_default_bounds(tmp_path):
     assert all(c[1] in autotune.BLOCKS and -(-c[0] // c[1]) <= 16 for c in classes)
     mxs.Batch(ctx, 64 << 20, 8, classes=classes).close()
     ctx.close()
+
+
+def _tuned(tmp_path, fmt):
+    """A 27-point grid kept by diagonals (2^17 entries and more) tuned with an
+    empty cache; (options, timings in ms, cache file)."""
+    import torch
+    from paper_2103_10116_amd import autotune, mxs
+    ctx = mxs.Context(0)
+    A = I.stencil27(64)
+    M = mxs.Matrix.from_host(ctx, A)
+    cache = str(tmp_path / "tune.json")
+    opts = autotune.tune_spmv(ctx, M, "f64", reps=10, cache=cache, fmt=fmt)
+    (entry,) = json.load(open(cache)).values()
+    M.close()
+    ctx.close()
+    return opts, entry["timings_ms"]
+
+
+@pytest.mark.parametrize("fmt", ["csr", "coo"])
+def test_the_untuned_choice_is_a_candidate(tmp_path, fmt):
+    """The products that only a matrix without options takes are timed too, and
+    win where they are several times faster: 27-point 64^3, a product over
+    diagonals against any kernel that can be asked for."""
+    opts, timings = _tuned(tmp_path, fmt)
+    plain = json.dumps({fmt + "_kernel": "auto"}, sort_keys=True)
+    assert plain in timings
+    assert opts == json.loads(plain) and timings[plain] == min(timings.values())
+
+
+def test_entries_of_other_candidates_are_not_served(tmp_path, monkeypatch):
+    """A choice cached before a candidate was added, or by another build of the
+    library, is timed again."""
+    from paper_2103_10116_amd import autotune, mxs
+    ctx = mxs.Context(0)
+    M = mxs.Matrix.from_host(ctx, I.poisson3d(12))
+    cache = str(tmp_path / "tune.json")
+    lines = []
+
+    def tune():
+        lines.clear()
+        autotune.tune_spmv(ctx, M, "f64", reps=2, cache=cache, log=lines.append, fmt="coo")
+        return len(lines)
+
+    monkeypatch.setitem(autotune.CANDIDATES, "coo", autotune.COO_CANDIDATES[-3:])
+    assert tune() == 3 and tune() == 0
+    monkeypatch.setitem(autotune.CANDIDATES, "coo", autotune.COO_CANDIDATES)
+    assert tune() == len(autotune.COO_CANDIDATES) and tune() == 0
+    monkeypatch.setattr(autotune, "_library", lambda: "another build")
+    assert tune() == len(autotune.COO_CANDIDATES)
+    M.close()
+    ctx.close()
