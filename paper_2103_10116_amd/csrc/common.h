@@ -163,8 +163,10 @@ struct CsrPart {
   // AUTO for irregular matrices: the two-pass product instead (no panel copy
   // is kept; `panels` is then only what the panel rule would take)
   BinPart bin;
-  // AUTO for matrices of few diagonals: read instead of the arrays above
+  // AUTO for matrices of few diagonals: read instead of the arrays above;
+  // whether they were looked for (conversions take the answer over)
   DiagPart diag;
+  bool diag_known = false;
 };
 
 // COO: equal chunks of block_nnz entries, one wave per chunk.  Rows cut by

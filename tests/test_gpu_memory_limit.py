@@ -206,3 +206,24 @@ def test_solve_without_room_for_partial_sums(orc):
     small.close()
     ctx.close()
     assert not al.live
+
+
+@pytest.mark.parametrize("fmt,dt", [("csr", "f64"), ("csr", "f32"), ("csr", "f16"),
+                                    ("coo", "f64"), ("coo", "f32"), ("ell", "f32"),
+                                    ("hyb", "f64")])
+def test_conversion_takes_the_sources_diagonals(orc, fmt, dt):
+    """A source kept by diagonals hands its diagonals on: the conversion makes
+    no table of its own to find them again (nothing allocated is freed)."""
+    import torch
+    A = I.stencil27(32)
+    al = Limited()
+    ctx = mxs.Context(0, allocator=al)
+    M = mxs.Matrix.from_host(ctx, A)
+    frees = al.frees
+    B = M.convert(fmt, dt)
+    assert al.frees == frees
+    M.close()                                       # B stands by itself
+    _check(orc, torch, ctx, A, B, fmt, dt)
+    B.close()
+    ctx.close()
+    assert not al.live
