@@ -3,7 +3,11 @@
 One timed step = one SpMV y = A x in each of the four formats (CSR, COO,
 ELL, hybrid) and both value types (FP64, FP32) on the 27-point stencil
 matrix of a 128^3 grid (n = 2,097,152, nnz = 55,742,968), inputs resident
-in HBM.  `value` is the step's algorithmic bytes divided by its time.
+in HBM.  `value` is the bytes of the step's formats (each array once,
+column and row indices included) divided by its time; products over
+diagonals read no indices, so `config.moved_GBs` gives the rate of what the
+step's products read and write at least, which is what `roofline` and every
+`frac_*` are of.
 Alongside, the run measures the attainable HBM bandwidth, every format on
 the power-law matrices (n = 2^20, MALL flushed between repetitions), the
 Krylov solvers on the 128^3 Poisson and convection-diffusion matrices,
@@ -51,6 +55,26 @@ def spmv_bytes(fmt, desc, vb, xb, beta_nonzero=False):
         return nnz * (vb + 4) + vec
     K, stride, cn = desc["ell_width"], desc["ell_stride"], desc["coo_nnz"]
     return (nnz - cn) * (vb + 4) + cn * (vb + 8) + vec
+
+
+def by_diagonals(fmt, desc, vb, max_row):
+    """Whether a stencil matrix keeps the second copy of its values that its
+    product reads instead of the format's arrays: it owns V bytes an entry more
+    than the format takes."""
+    n, nnz = desc["nrows"], desc["nnz"]
+    own = {"csr": nnz * (vb + 4) + 4 * n, "coo": nnz * (vb + 8)}.get(fmt)
+    if own is None:
+        own = desc["ell_width"] * desc["ell_stride"] * (vb + 4) + desc["coo_nnz"] * (vb + 8)
+    return max_row <= 64 and desc["bytes"] > own + 0.9 * nnz * vb
+
+
+def moved_bytes(fmt, desc, vb, xb, max_row):
+    """What the product has to read and write: the format's arrays, or (over
+    diagonals, as many as the longest row has entries) the values by diagonals
+    and a byte a row, and the vectors."""
+    if by_diagonals(fmt, desc, vb, max_row):
+        return desc["nrows"] * (max_row * vb + 1 + 2 * xb)
+    return spmv_bytes(fmt, desc, vb, xb)
 
 
 def ell_streamed_bytes(desc, vb, xb):
@@ -107,15 +131,16 @@ def measured_traffic(fmt, dt, info, max_row):
     nt_ell = big(info["ell_width"] * info["ell_stride"] * (4 + vb))
     wpg = info["waves_per_group"]
     chunked = -(-info["blocks"] // wpg) * 64 * wpg  # threads of the stream/COO grid
-    # the product over diagonals, if the summary's step ran it for this type
-    # (the same kernel whatever the format; nine diagonals, or three threes,
-    # a round)
+    # the product over diagonals, if this matrix runs it (AUTO does on the
+    # step's matrix) and the summary's step did for this type: the same kernel
+    # whatever the format; nine diagonals, or three threes, a round
     nt_diag = big(max_row * info["nrows"] * vb)
     grid = -(-info["nrows"] // 256) * 256
-    for shape in ("3,true,true", "9,false,true"):
-        k = (f"k_diag<{t},false,0,{nt_diag},{shape}>", grid)
-        if k in table:
-            return int(table[k])
+    if "bytes" not in info or by_diagonals(fmt, info, vb, max_row):
+        for shape in ("3,true,true", "9,false,true"):
+            k = (f"k_diag<{t},false,0,{nt_diag},{shape}>", grid)
+            if k in table:
+                return int(table[k])
     keys = []
     ck = info["csr_kernel"]
     if fmt == "csr" and ck == 4:  # products through LDS
@@ -235,21 +260,26 @@ def main():
         for dt in ("f64", "f32"):
             mats[(fmt, dt)] = M if (fmt, dt) == ("csr", "f64") else M.convert(fmt, dt)
     per = {}
-    step_bytes = 0
+    step_bytes = step_moved = 0
+    max_row = int(A.row_lengths().max())
     for (fmt, dt), B in mats.items():
         vb = 8 if dt == "f64" else 4
         nbytes = spmv_bytes(fmt, B.info(), vb, vb)
         step_bytes += nbytes
+        moved = moved_bytes(fmt, B.info(), vb, vb, max_row)
+        step_moved += moved
         fn = lambda B=B, dt=dt: mxs.spmv(ctx, B, xd[dt], yd[dt])
         for _ in range(args.warmup):
             fn()
         t, _ = timer.time(fn, max(args.steps, 10))
         per[f"{fmt}_{dt}"] = {"us": round(t * 1e6, 2), "GBs": round(nbytes / t / 1e9, 1),
-                              "bytes": nbytes,
-                              "frac_spec": round(nbytes / t / 1e9 / PEAK_HBM_GBS, 4)}
+                              "bytes": nbytes, "moved_bytes": moved,
+                              "moved_GBs": round(moved / t / 1e9, 1),
+                              "frac_spec": round(moved / t / 1e9 / PEAK_HBM_GBS, 4)}
         if peak_meas:
-            per[f"{fmt}_{dt}"]["frac_measured"] = round(nbytes / t / 1e9 / peak_meas, 4)
-        log(f"stencil27 {fmt} {dt}: {t*1e6:.1f} us  {nbytes/t/1e9:.0f} GB/s")
+            per[f"{fmt}_{dt}"]["frac_measured"] = round(moved / t / 1e9 / peak_meas, 4)
+        log(f"stencil27 {fmt} {dt}: {t*1e6:.1f} us  {moved/t/1e9:.0f} GB/s moved, "
+            f"{nbytes/t/1e9:.0f} GB/s of format bytes")
 
     def step():
         for (fmt, dt), B in mats.items():
@@ -273,22 +303,24 @@ def main():
     out["config"] = {"workload": f"SpMV y=Ax, 27-point stencil {N}^3 (n={A.n}, nnz={A.nnz}), "
                                  "CSR+COO+ELL+HYB x FP64+FP32 per step",
                      "n": A.n, "nnz": A.nnz, "step_bytes": step_bytes,
+                     "value_counts": "format bytes, indices included",
+                     "moved_bytes": step_moved,
+                     "moved_GBs": round(step_moved / (ms_step * 1e-3) / 1e9, 1),
                      "wall_s_timed": round(wall, 4)}
     # dominant kernel: the slowest of the step
     dom = max(per, key=lambda k: per[k]["us"])
     d = per[dom]
     fmt_d, dt_d = dom.split("_")
     # bytes a launch moves: from the counters when they are of this source, else
-    # the format's (the product over diagonals reads no column indices, so its
-    # rate over the format's bytes, `GBs` above, is no bandwidth)
-    traffic = measured_traffic(fmt_d, dt_d, mats[(fmt_d, dt_d)].info(),
-                               int(A.row_lengths().max()))
-    moved = traffic if traffic else d["bytes"]
+    # what the product has to move
+    traffic = measured_traffic(fmt_d, dt_d, mats[(fmt_d, dt_d)].info(), max_row)
+    moved = traffic if traffic else d["moved_bytes"]
     rate = round(moved / (d["us"] * 1e-6) / 1e9, 1)
     out["roofline"] = {"bound": "hbm", "kernel": f"spmv_{dom}", "achieved": rate,
                        "peak": PEAK_HBM_GBS, "unit": "GB/s",
                        "frac": round(rate / PEAK_HBM_GBS, 4),
                        "bytes_per_launch": moved, "us_per_launch": d["us"],
+                       "bytes_from": "counters" if traffic else "model",
                        "format_bytes": d["bytes"], "traffic": traffic}
     if peak_meas:
         out["roofline"]["measured_peak"] = round(peak_meas, 1)
@@ -487,7 +519,8 @@ def main():
             bq = torch.zeros(Q.n, dtype=torch.float64, device=dev)
             mxs.spmv(ctx, Qm, xstar, bq)
             xq = torch.zeros_like(bq)
-            csr_b = Q.nnz * 12 + 4 * (Q.n + 1) + 16 * Q.n
+            # bytes of a product (by diagonals: without column indices)
+            csr_b = moved_bytes("csr", Qm.info(), 8, 8, int(Q.row_lengths().max()))
             if system not in spmv_cw:
                 yq = torch.zeros_like(bq)
                 fn = lambda Qm=Qm, yq=yq: mxs.spmv(ctx, Qm, xstar, yq)
@@ -515,14 +548,14 @@ def main():
             sols.setdefault(system, {})[("krylov", name)] = xq.cpu().numpy()
             # fixed 1000 iterations (no convergence test can stop it), for
             # GFLOP/s and GB/s under the per-iteration models: CG 2nnz+10n
-            # flops and B_csr+64n bytes; BiCGSTAB 4nnz+20n and 2B_csr+120n
-            # when the products form r_hat.v and (t.s, t.t) (rows-from-LDS
-            # CSR: r_hat read by the first product), else 2B_csr+144n;
-            # pipelined CG 2nnz+16n and B_csr+104n (q, z, w, s, r, p, x read,
-            # z, s, p, x, r, w written); CGS 4nnz+19n and 2B_csr+128n (the
-            # product forms r_hat.v), else 2B_csr+136n;
-            # GMRES(30) step j 2nnz+8(j+1)n+3n
-            # and B_csr+(4(j+1)+9)8n, averaged over j = 0..29
+            # flops and B+64n bytes (B: the product's); BiCGSTAB 4nnz+20n and
+            # 2B+120n when the products form r_hat.v and (t.s, t.t)
+            # (rows-from-LDS CSR and diagonals: r_hat read by the first
+            # product), else 2B+144n; pipelined CG 2nnz+16n and B+104n (q, z,
+            # w, s, r, p, x read, z, s, p, x, r, w written); CGS 4nnz+19n and
+            # 2B+128n (the product forms r_hat.v), else 2B+136n; GMRES(30)
+            # step j 2nnz+8(j+1)n+3n and B+(3(j+1)+5)8n, averaged over
+            # j = 0..29, with 32 vectors read or written a cycle for x
             n_, z_ = Q.n, Q.nnz
             own_dots = Qm.info()["csr_kernel"] == mxs.CSR_ROWS_LDS
             fl, by = {"cg": (2 * z_ + 10 * n_, csr_b + 64 * n_),
@@ -531,7 +564,7 @@ def main():
                                    2 * csr_b + (120 if own_dots else 144) * n_),
                       "cgs": (4 * z_ + 19 * n_, 2 * csr_b + (128 if own_dots else 136) * n_),
                       "gmres": (2 * z_ + 8 * 15.5 * n_ + 3 * n_,
-                                csr_b + (4 * 15.5 + 9) * 8 * n_)}[solver]
+                                csr_b + (3 * 15.5 + 5 + 32 / 30) * 8 * n_)}[solver]
             xq.zero_()
             torch.cuda.synchronize()
             t0 = time.perf_counter()

@@ -322,7 +322,8 @@ typedef struct {
   double rel_tol;           /* stop when ||r|| <= max(rel_tol*baseline, abs_tol) */
   double abs_tol;
   int32_t baseline;         /* MXS_BASELINE_* */
-  int32_t check_every;      /* at most this many iterations are queued ahead of the count the device reports (0 = default) */
+  int32_t check_every;      /* the host queues at most min(check_every, 4) + 4 iterations beyond the count that the
+                               device last reported (0 = default: 8); GMRES and small CG take no notice of it */
   int32_t max_replacements; /* true-residual replacements before NOT_CONVERGED (default 3 if < 0) */
 } mxs_stop;
 

@@ -727,7 +727,7 @@ __global__ __launch_bounds__(BS) void k_batch_cg(const SlotDesc* __restrict__ de
       // (explicit LDS addresses: from an offset into a generic pointer the
       // compiler would make flat loads)
       typedef __attribute__((address_space(3))) const double lds_double;
-      const uint32_t base =
+      const uint32_t lds0 =
           (uint32_t)(uintptr_t)(__attribute__((address_space(3))) double*)dyn;
       auto spmv_reg = [&](const double* __restrict__, double (&q)[RPT]) {
         // (unpacked anew by every product, instead of once before the loop
@@ -741,7 +741,7 @@ __global__ __launch_bounds__(BS) void k_batch_cg(const SlotDesc* __restrict__ de
           for (int j = 0; j < ML; ++j) {
             const int t = k * ML + j;
             const uint32_t c = t & 1 ? cr[t / 2] >> 16 : cr[t / 2] & 0xFFFFu;
-            acc += vr[t] * *(lds_double*)(uintptr_t)(base + c);
+            acc += vr[t] * *(lds_double*)(uintptr_t)(lds0 + c);
           }
           q[k] = acc;
         }

@@ -25,8 +25,8 @@
 //
 // Power-law rows, 2^20 columns, cold, us (column panels of the merge and COO
 // kernels -> this): s = 1.79 (16.9M entries) FP64 129 -> 70, FP32 116 -> 47;
-// s = 2.0 (6.4M) FP64 71 -> 41, FP32 49 -> 25.  Pass 1 takes 49 of the 70 us
-// (237 MB, 4.8 TB/s), pass 2 the other 22.
+// s = 2.0 (6.4M) FP64 71 -> 41, FP32 49 -> 32.  Pass 1 takes 49 of the 70 us,
+// pass 2 the other 21.
 #include <algorithm>
 #include <initializer_list>
 #include <type_traits>

@@ -72,14 +72,14 @@ namespace mxs {
 // bins and `panels` column panels of `width` columns.  acol/aval (column
 // within the panel, its top bit set where a partial sum ends; value) are in
 // pass 1's order: panel, batch of bins, bin, row; tiles in whole runs of 8
-// entries, a panel's share of a batch in whole chunks of 64 runs; a chunk's values as
-// 16-byte words, word w of all its runs side by side.  rbase: where the
-// first partial sum of the run's tile in its chunk goes.  perm holds, in row order, the slots of the bin's
-// partial sums with the top bit set at a row's first (from run brun[b], 8 a
-// run), grank the rank within the bin of the row each run starts in, rowlist
-// the bins' non-empty rows (from brank[b]).  bent: the bins' first entries;
-// bpart, blen: their partial sums; tile_a, tile_b: first run and first
-// partial sum of each tile.  Batches of bins (batch, first partial sum
+// entries, a panel's share of a batch in whole chunks of 64 runs; a chunk's
+// values as 16-byte words, word w of all its runs side by side.  rbase: where
+// the first partial sum of the run's tile in its chunk goes.  perm holds, in
+// row order, the slots of the bin's partial sums with the top bit set at a
+// row's first (from run brun[b], 8 a run), grank the rank within the bin of
+// the row each run starts in, rowlist the bins' non-empty rows (from
+// brank[b]).  bent: the bins' first entries; bpart, blen: their partial sums;
+// tile_a, tile_b: first run and first partial sum of each tile.  Batches of bins (batch, first partial sum
 // batch_base) have partial sums that fit the fixed scratch; work holds pass
 // 1's jobs (panel, first and past-the-last chunk): list 0 (from work_at[0])
 // for all bins, list q + 1 for batch q when there are several.
@@ -278,8 +278,8 @@ mxs_status launch_spmv(mxs_ctx* ctx, const mxs_matrix* A, const void* alpha, con
 // nv = 2 also of y[i]^2, interleaved (dpart[b * nv + v]): returns how many
 // work-group partials (<= kDotPartials) were written, or 0 when A's kernel
 // has no such form (then nothing was enqueued and the caller forms the dots
-// itself).  The merge path forms x.y only; w != x or nv = 2 need the
-// rows-from-LDS kernel.
+// itself).  The merge path forms x.y only; w != x or nv = 2 need a product
+// over diagonals, in two passes or by the rows-from-LDS kernel.
 constexpr int kDotPartials = 4096;
 int launch_spmv_dot(mxs_ctx* ctx, const mxs_matrix* A, const void* x, void* y,
                     const int32_t* skip, double* dpart, const void* w = nullptr, int nv = 1);

@@ -461,8 +461,9 @@ __global__ void k_panel_refresh(int64_t m, int64_t n, int64_t W,
 // this form.
 constexpr int kTable = 1024;
 // Where the diagonals pay.  Entries: below 2^17 products are launches either
-// way (27-point 40^3, 1.6M entries: FP64 7.4 -> 6.4 us; 7-point 48^3, 0.76M:
-// 6.3 -> 6.1) and the set-up would only cost.  Slots per entry: a slot is V
+// way (27-point 40^3, 1.6M entries: FP64 10.2 -> 8.6 us from HBM, 6.0 -> 5.8
+// repeated; 7-point 48^3, 0.76M: 8.0 -> 6.5, 5.9 -> 6.0) and the set-up would
+// only cost.  Slots per entry: a slot is V
 // bytes against an entry's V + 4, so 1.2 leaves FP64 a fifth.
 constexpr int64_t kDiagMinEntries = int64_t(1) << 17;
 constexpr double kDiagMaxFill = 1.2;

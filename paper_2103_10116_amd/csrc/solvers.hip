@@ -1458,8 +1458,9 @@ Stop read_stop(const mxs_stop* s, int64_t default_max) {
 }
 
 // Reads the word that the kernels report to until the count has reached
-// `target` (the last count up to it that they send) or the solve (or GMRES cycle) has ended (*ended).  A stream that
-// has nothing left to run by then is read itself: a solve cannot hang here.
+// `target` (the last count up to it that they send) or the solve (or GMRES
+// cycle) has ended (*ended).  A stream that has nothing left to run by then is
+// read itself: a solve cannot hang here.
 mxs_status await_iters(mxs_ctx* ctx, Work& w, int64_t target, int64_t* seen, bool* ended,
                        const char* what) {
   target -= target > 0 ? target % kPostEvery : 0;
@@ -1488,14 +1489,16 @@ mxs_status await_iters(mxs_ctx* ctx, Work& w, int64_t target, int64_t* seen, boo
 }
 
 // Enqueues iteration(k0), iteration(k0 + 1), ... until the device status is
-// set, staying at most min(C, kAhead) iterations ahead of the last count that
-// the kernels have sent; returns with the final state in w.hst.  The
-// iterations queued beyond the last one return at once in every kernel, but
-// each of their launches still takes 2 to 3 us.  With 16 to 32 of them and a
-// copy of the state every 16 iterations, as a host that waits for copies
-// needs, 21 iterations of Jacobi CG on 2^18 rows take 1.11 ms, with at most 7
-// and no copies 0.95; 150 of CG on the 7-point grid 40^3 2.08 and 1.84;
-// refinement on 120^3, 5 inner solves, 5.98 and 5.70.
+// set, and before the next one waits until the device has sent the last
+// multiple of kPostEvery up to min(C, kAhead) before the iterations enqueued:
+// at most min(C, kAhead) + kPostEvery of them are beyond the count that it has
+// sent.  Returns with the final state in w.hst.  The iterations queued beyond
+// the last one return at once in every kernel, but each of their launches
+// still takes 2 to 3 us.  With 16 to 32 of them and a copy of the state every
+// 16 iterations, as a host that waits for copies needs, 21 iterations of
+// Jacobi CG on 2^18 rows take 1.11 ms, with at most 8 and no copies 0.95; 150
+// of CG on the 7-point grid 40^3 2.08 and 1.84; refinement on 120^3, 5 inner
+// solves, 5.98 and 5.70.
 constexpr int64_t kAhead = 4;
 
 void mail_reset(Work& w, int64_t k) {

@@ -1256,15 +1256,17 @@ __global__ __launch_bounds__(64 * W) void k_ell(int64_t n, int64_t K, int64_t ld
 // ---------------------------------------------------------------------------
 // Matrices of few diagonals (see DiagPart), any format, one lane a row and one
 // wave a slice.  Bound by memory: D values, one byte, x and y a row, where the
-// formats' own kernels read an index (two in COO) an entry as well.  27-point
-// 128^3, us (format's kernel -> this): CSR FP64 137 -> 89 (470 MB, 5.3 TB/s;
-// 64 of them the values, 15 the gathers, 10 the y stores), FP32 89 -> 46, FP16
-// 77 -> 32; COO FP64 170 -> 91; ELL FP32 86 -> 46; 7-point 128^3 CSR FP64 44 ->
-// 32 cold, 31 -> 22 from the Infinity Cache, FP16 27 -> 12.  The x of a group of three neighbouring diagonals is one load:
-// the middle one's, whose lanes hand theirs to the next lane up and down, with
-// the two that lie outside the slice read by the edge lanes.  A round's loads
-// are in flight together; no LDS (27-point FP64 96 us with a load a
-// diagonal; 98 with each row's offsets from a table in LDS).
+// formats' own kernels read an index (two in COO) an entry as well.  128^3
+// grids, us from HBM (repeated, where the Infinity Cache holds what it can),
+// format's kernel -> this: 27-point CSR FP64 146 -> 94 (138 -> 89: 491 MB by
+// the counters, 5.5 TB/s; 64 us of them the values, 15 the gathers, 10 the y
+// stores), FP32 92 -> 47 (86 -> 34), FP16 78 -> 32 (75 -> 22), COO FP64 (170 ->
+// 89); 7-point CSR FP64 44 -> 33 (31 -> 22), FP32 30 -> 19 (22 -> 13), FP16 29
+// -> 16 (20 -> 11).  The x of a group of three neighbouring diagonals is one
+// load: the middle one's, whose lanes hand theirs to the next lane up and down,
+// with the two that lie outside the slice read by the edge lanes (27-point
+// FP64 96 us, FP32 46 with a load a diagonal; FP64 98 with each row's offsets
+// from a table in LDS).  A round's loads are in flight together; no LDS.
 //
 // Each work-group takes R times 4 slices.  NV > 0: it also stores the sum of
 // w[i] * y[i] over its rows to part[blockIdx.x * NV], and with NV = 2 the sum
@@ -1412,7 +1414,10 @@ template <typename V>
 constexpr bool kDiagValue = std::is_same_v<V, double> || std::is_same_v<V, float> ||
                             std::is_same_v<V, _Float16>;
 
-// nv > 0: at most kDotPartials work-groups, whose number is returned
+// nv > 0: at most kDotPartials work-groups, whose number is returned.  Products
+// that form dots keep ordinary loads whatever the size (CG on 27-point 128^3,
+// 453 MB of values: 136 us an iteration, 128 with non-temporal ones; 7-point
+// 200^3, 448 MB: 226 and 206).
 template <typename V, typename T, bool SCALED>
 int launch_diag(mxs_ctx* ctx, const mxs_matrix* A, const DiagPart& P, const float* scale, T alpha,
                 const T* x, T beta, T* y, const int32_t* skip, const T* w = nullptr,
@@ -2086,10 +2091,10 @@ void* noalloc_scratch(int device) {
 }
 
 // y = A x together with work-group partial sums of x[i] * y[i] (CG's p.q),
-// for the kernels that write each row's result once from one lane: the
-// rows-from-LDS CSR kernel and the column-panel merge path (whose last pass
-// forms the rows).  Returns the number of partials written to dpart (at most
-// kDotPartials), or 0 when A's kernel has no such form (nothing enqueued).
+// for the kernels that write each row's result once from one lane: products
+// over diagonals and in two passes, the rows-from-LDS CSR kernel and the
+// column-panel merge path (whose last pass forms the rows).  Returns the number
+// of partials written to dpart (at most kDotPartials), or 0 when A's kernel has no such form (nothing enqueued).
 template <typename V, typename T, bool SCALED>
 int launch_dot_typed(mxs_ctx* ctx, const mxs_matrix* A, const T* x, T* y, const int32_t* skip,
                      double* dpart, void* scratch, const T* w, int nv) {

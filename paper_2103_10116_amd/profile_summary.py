@@ -10,8 +10,9 @@
 count and mean / median duration.  `traffic` records FETCH_SIZE and
 WRITE_SIZE per dispatch (KiB) for the SpMV and CG kernels, the scale factors
 measured on the HBM probe's copy kernel (it reads and writes probe_bytes,
-the probe's array size), and the SHA-256 of spmv.hip at measurement time, so that a later reader can tell
-whether the counters still describe the current kernels.  `counters` merges
+the probe's array size), and the SHA-256 of the products' sources (spmv.hip,
+binned.hip) at measurement time, so that a later reader can tell whether the
+counters still describe the current kernels.  `counters` merges
 the passes of one workload (one counter set per run) into one table per
 kernel and grid, with the ratios derived from them: L2 hit rate, mean
 latency of the vector cache's L2 reads and of the L2's reads beyond it (by
@@ -29,12 +30,15 @@ import os
 import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-SPMV_SRC = os.path.join(HERE, "csrc", "spmv.hip")
+SPMV_SRC = [os.path.join(HERE, "csrc", f) for f in ("spmv.hip", "binned.hip")]
 
 
 def spmv_source_sha() -> str:
-    with open(SPMV_SRC, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+    h = hashlib.sha256()
+    for path in SPMV_SRC:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
 def _short(name: str) -> str:
@@ -43,7 +47,7 @@ def _short(name: str) -> str:
 
 
 def stats(trace_csv: str, out: str, command: str, top: int = 30,
-          always=("k_csr", "k_coo", "k_ell", "k_cg")) -> None:
+          always=("k_csr", "k_diag", "k_bin", "k_coo", "k_ell", "k_cg")) -> None:
     """Per-kernel summary: the `top` kernel/grid pairs by total time, then
     every SpMV or CG kernel (names starting with one of `always`) not among
     them."""
@@ -97,7 +101,8 @@ def traffic(fetch_csv: str, write_csv: str, out: str, command: str,
              "# kernel grid fetch_kib write_kib scaled_bytes"]
     for k in sorted(fe):
         name, grid = k
-        if not name.startswith(("k_csr", "k_diag", "k_bin", "k_coo", "k_ell", "k_panel", "k_cg", "k_probe")):
+        if not name.startswith(("k_csr", "k_diag", "k_bin", "k_coo", "k_ell", "k_panel", "k_cg",
+                                "k_probe")):
             continue
         f_ = fe[k]
         w_ = wr.get(k, 0.0)

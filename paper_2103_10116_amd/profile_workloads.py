@@ -9,6 +9,7 @@ cached beyond L2 residue):
 
   powerlaw   n = 2^20 power-law matrices, s = 1.79 (mean 16) and s = 2.0:
              CSR FP64 / FP32 / row-scaled FP16 and COO FP64 / FP32, cold
+             (powerlaw1.79, powerlaw2.0: one of them)
   spd        the random SPD matrix of n = 2^20: CSR FP64 / FP32 / FP16, cold
   stencil27  the 27-point 128^3 matrix: CSR, COO, ELL FP64 and the 7-point
              128^3 CSR FP64 (warm: the 27-point matrix is larger than the cache)
@@ -85,8 +86,8 @@ def main():
                 B.close()
 
     for w in args.workloads.split(","):
-        if w == "powerlaw":
-            for s in (1.79, 2.0):
+        if w.startswith("powerlaw"):
+            for s in (1.79, 2.0) if w == "powerlaw" else (float(w[len("powerlaw"):]),):
                 Z = mxs.Matrix.from_host(ctx, I.zipf_random(2 ** 20, s, 4096))
                 run(f"powerlaw_s{s}", Z, [("csr", "f64"), ("csr", "f32"), ("csr", "f16"),
                                           ("coo", "f64"), ("coo", "f32")], True)

@@ -97,3 +97,26 @@ def test_fastest_refinement_ignores_preconditioned_and_failed_rows():
     assert best == {"variant": "ir_f32_carry", "speedup_vs_plain": 1.11,
                     "literal_ir_f32_speedup_vs_plain": 0.91}
     assert bench.fastest_refinement({"plain_f64_cg": {"time_s": 1.0}}) is None
+
+
+def test_moved_bytes_follow_the_product_that_runs():
+    """A matrix kept by diagonals (its second copy of the values shows in its
+    bytes) is charged for what that product reads; one whose kernel was asked
+    for, or of long rows, for its format's arrays, and never given the traffic
+    of the product over diagonals."""
+    n, nnz = 128 ** 3, 55742968
+    base = {"block_nnz": 256, "waves_per_group": 4, "blocks": -(-nnz // 256), "coo_kernel": 1,
+            "csr_kernel": 0, "lanes_per_row": 0, "nrows": n, "nnz": nnz, "ell_width": 0,
+            "ell_stride": n, "coo_nnz": nnz}
+    for vb, dt in ((8, "f64"), (4, "f32")):
+        own = nnz * (vb + 8)
+        asked, auto = dict(base, bytes=own), dict(base, bytes=own + n * (27 * vb + 1))
+        assert bench.moved_bytes("coo", auto, vb, vb, 27) == n * (27 * vb + 1 + 2 * vb)
+        assert bench.moved_bytes("coo", asked, vb, vb, 27) == bench.spmv_bytes("coo", asked, vb, vb)
+        assert bench.moved_bytes("coo", auto, vb, vb, 65) == bench.spmv_bytes("coo", auto, vb, vb)
+        diag = bench.measured_traffic("coo", dt, auto, 27)
+        assert diag and bench.measured_traffic("coo", dt, asked, 27) != diag
+        csr = dict(base, csr_kernel=4, bytes=nnz * (vb + 4) + 4 * (n + 1) + 8 * n // 64)
+        assert bench.moved_bytes("csr", csr, vb, vb, 27) == bench.spmv_bytes("csr", csr, vb, vb)
+        ell = dict(base, ell_width=27, coo_nnz=0, bytes=27 * n * (vb + 4) + n * (27 * vb + 1))
+        assert bench.moved_bytes("ell", ell, vb, vb, 27) == n * (27 * vb + 1 + 2 * vb)
