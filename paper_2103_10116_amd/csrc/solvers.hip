@@ -847,6 +847,8 @@ __global__ __launch_bounds__(RB) void k_gm_xupdate(int64_t n, int64_t ldv,
                                                    const double* __restrict__ V,
                                                    double* __restrict__ x, const KState* st) {
   if (st->done) return;
+  constexpr int U = 8;  // loads in flight
+  static_assert(MAXM % U == 0, "whole groups of vectors");
   __shared__ double y[MAXM], sc[MAXM];
   const int k = st->k;
   if (threadIdx.x < MAXM) {
@@ -856,9 +858,13 @@ __global__ __launch_bounds__(RB) void k_gm_xupdate(int64_t n, int64_t ldv,
   __syncthreads();
   GRID_STRIDE(r, n) {
     double xr = x[r];
+    for (int i = 0; i < k; i += U) {
+      double vr[U];
 #pragma unroll
-    for (int i = 0; i < MAXM; ++i)
-      if (i < k) xr += y[i] * (sc[i] * V[i * ldv + r]);
+      for (int u = 0; u < U; ++u) vr[u] = i + u < k ? V[(i + u) * ldv + r] : 0.0;
+#pragma unroll
+      for (int u = 0; u < U; ++u) xr += y[i + u] * (sc[i + u] * vr[u]);
+    }
     x[r] = xr;
   }
 }
