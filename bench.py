@@ -278,6 +278,8 @@ def main():
                               "frac_spec": round(moved / t / 1e9 / PEAK_HBM_GBS, 4)}
         if peak_meas:
             per[f"{fmt}_{dt}"]["frac_measured"] = round(moved / t / 1e9 / peak_meas, 4)
+        # (repeated products find up to 256 MiB of it in the Infinity Cache)
+        per[f"{fmt}_{dt}"]["cache_assisted"] = moved <= 256 * (1 << 20)
         log(f"stencil27 {fmt} {dt}: {t*1e6:.1f} us  {moved/t/1e9:.0f} GB/s moved, "
             f"{nbytes/t/1e9:.0f} GB/s of format bytes")
 
