@@ -182,7 +182,8 @@ typedef struct {
                               (CSR, COO, and the COO part of HYB; no row beyond some 30000 entries),
                               the product runs in two streaming passes over a second copy of the
                               entries instead (10 to 16 bytes an entry); info and exports are as
-                              above.
+                              above.  (FP64 CSR whose neighbouring rows share their columns, up to 4
+                              MiB of x, takes them inside the solvers only.)
                               In the same way matrices of at least 2^17 entries on at most 64
                               diagonals (rows of at most 64 entries, at most 255 different sets of
                               diagonals, at most a fifth of them holes) run, in any format, over a

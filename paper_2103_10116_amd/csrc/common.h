@@ -161,8 +161,11 @@ struct CsrPart {
   // over the panel copy (row-scaled FP16 keeps the merge kernel)
   int32_t* srow = nullptr;
   // AUTO for irregular matrices: the two-pass product instead (no panel copy
-  // is kept; `panels` is then only what the panel rule would take)
+  // is kept; `panels` is then only what the panel rule would take).  near:
+  // neighbouring rows share their columns, so that products by themselves stay
+  // on the merge path (crow is kept) and only the solvers' run in two passes
   BinPart bin;
+  bool near = false;
   // AUTO for matrices of few diagonals: read instead of the arrays above;
   // whether they were looked for (conversions take the answer over)
   DiagPart diag;
@@ -271,8 +274,9 @@ inline size_t value_bytes(mxs_dtype dt) {
 // launchers shared between translation units (all enqueue on ctx->stream)
 // skip (nullable, device): when *skip != 0 every kernel of the product
 // returns at once (solvers queue iterations past convergence this way)
+// single: a product by itself, not a solver's (see CsrPart::near)
 mxs_status launch_spmv(mxs_ctx* ctx, const mxs_matrix* A, const void* alpha, const void* x,
-                       const void* beta, void* y, const int32_t* skip);
+                       const void* beta, void* y, const int32_t* skip, bool single = false);
 // y = A x (square A) and, in the same launches, work-group partial sums of
 // w[i] * y[i] in dpart (w = x when NULL: CG's p.q with x = p), and with
 // nv = 2 also of y[i]^2, interleaved (dpart[b * nv + v]): returns how many
@@ -295,7 +299,7 @@ void* noalloc_scratch(int device);
 // matrix's bins need is possible.
 mxs_status launch_spmv_scratch(mxs_ctx* ctx, const mxs_matrix* A, const void* alpha,
                                const void* x, const void* beta, void* y, const int32_t* skip,
-                               void* scratch, size_t bytes);
+                               void* scratch, size_t bytes, bool single);
 // The two-pass product (binned.hip): whether a matrix takes it, its set-up
 // from row-ordered entries (rp: host copy of the row pointers d_rp), its
 // launch (prod: prod_bytes of scratch, at least the largest batch's;

@@ -881,6 +881,58 @@ bool copy_wanted(const mxs_matrix* A, const mxs_convert_opts* o) {
                 o->lanes_per_row <= 0 && o->rows_per_group <= 0);
 }
 
+// Distinct 128-byte lines of an FP64 x among the columns of kNearEntries
+// consecutive entries, added up over kNearWindows windows spread over the matrix.
+constexpr int kNearEntries = 4096, kNearWindows = 256;
+__global__ __launch_bounds__(256) void k_near_lines(int64_t nnz, const int32_t* __restrict__ col,
+                                                    int32_t* __restrict__ lines) {
+  constexpr int N = 2 * kNearEntries;
+  __shared__ int32_t tab[N], cnt;
+  for (int q = threadIdx.x; q < N; q += 256) tab[q] = -1;
+  if (threadIdx.x == 0) cnt = 0;
+  __syncthreads();
+  const int64_t first = (nnz - kNearEntries) * blockIdx.x / (kNearWindows - 1);
+  for (int k = threadIdx.x; k < kNearEntries; k += 256) {
+    const int32_t line = col[first + k] >> 4;
+    // (at most half of the slots are ever taken)
+    for (uint32_t q = (uint32_t)line * 0x9E3779B1u % N;; q = (q + 1) % N) {
+      const int32_t old = atomicCAS(&tab[q], -1, line);
+      if (old == -1) atomicAdd(&cnt, 1);
+      if (old == -1 || old == line) break;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) atomicAdd(lines, cnt);
+}
+
+// Whether the rows' columns are near each other: at most 96 lines of x a window,
+// so that they stay in the vector cache from row to row and the merge path reads
+// little but the entries.  Rows of 80 entries within w columns of the diagonal,
+// 2^18 rows, merge path against two passes, us from HBM (repeated): w = 200 (29
+// lines) 60 (43) against 65 (49), w = 600 (78) 64 (43) against 65 (49), w = 1000
+// (128) 71 (46) against 66 (50), w = 2000 (253) 88 (63) against 66 (50); three
+// unknowns a node of a 27-point grid 48^3 (41) 73 (67) against 83 (73).  FP32 and
+// FP16 values gain in two passes there too (w = 200: 45 to 43 and 43 to 36).  So
+// do the solvers, whose dots the passes form (the grid at 40^3: CG 63 to 60, and
+// BiCGSTAB 122 to 116 us an iteration), and keep them for all of their products:
+// one product of each kind an iteration would draw both copies of the entries
+// through the Infinity Cache (CGS 118 by the merge path, 115 in two passes, 136
+// so).
+mxs_status rows_near(mxs_ctx* ctx, const mxs_matrix* A, bool* near) {
+  *near = false;
+  if (A->dt != MXS_F64 || A->nnz < kNearEntries) return MXS_OK;
+  if (!ws_reserve(ctx, 256)) return fail(ctx, MXS_OOM, "workspace");
+  // (the workspace's first word may hold a conversion's error flag)
+  int32_t* lines = (int32_t*)ctx->ws.ptr + 1;
+  int count = 0;
+  MXS_HIP_TRY(ctx, hipMemsetAsync(lines, 0, sizeof(int32_t), ctx->stream));
+  k_near_lines<<<kNearWindows, 256, 0, ctx->stream>>>(A->nnz, A->csr.col, lines);
+  MXS_HIP_TRY(ctx, hipGetLastError());
+  if (mxs_status st = read_err(ctx, lines, &count)) return st;
+  *near = count <= 96 * kNearWindows;
+  return MXS_OK;
+}
+
 mxs_status build_csr_merge(mxs_ctx* ctx, mxs_matrix* A, const mxs_convert_opts* opts,
                            int64_t max_row) {
   if (A->dt != MXS_F64 && A->dt != MXS_F32 && A->dt != MXS_F16_ROWSCALED)
@@ -905,6 +957,17 @@ mxs_status build_csr_merge(mxs_ctx* ctx, mxs_matrix* A, const mxs_convert_opts* 
     P.nempty = (int64_t)empty.size();
     P.empty_rows = upload(ctx, A, empty);
     if (!P.empty_rows) return fail(ctx, MXS_OOM, "merge-path CSR set-up");
+    std::vector<int32_t> crow;
+    int64_t bad = 0;
+    bool near = false;
+    if (panels <= 1)
+      if (mxs_status st = rows_near(ctx, A, &near)) return st;
+    if (near && merge_rows(rp, nnz, C, crow, &bad)) {
+      P.crow = upload(ctx, A, crow);
+      if (!P.crow) return fail(ctx, MXS_OOM, "merge-path CSR set-up");
+      P.near = true;
+    }
+    // (waits for the copies of the host vectors above)
     return build_bins(ctx, A, P.bin, n, A->ncols, nnz, rp, P.rowptr, P.col, P.val, A->dt);
   }
   if (panels > 1 && nnz > 0) return build_panels(ctx, A, panels, C);

@@ -30,7 +30,8 @@
 // Matrices of few diagonals (stencils) in any of these formats run k_diag over
 // a copy of their values by diagonals unless a kernel was asked for.
 // Irregular CSR, COO and HYB matrices large enough to gain from it run the
-// two-pass product of binned.hip unless a kernel was asked for.
+// two-pass product of binned.hip unless a kernel was asked for (FP64 CSR whose
+// neighbouring rows share their columns: only inside the solvers).
 //
 // Per-lane sequential chains are at most NPL (+ the scan depth of 6) for
 // CSR/COO blocks and at most a quarter of a row's entries per wave for long
@@ -1776,9 +1777,9 @@ void launch_binned(mxs_ctx* ctx, const BinPart& B, const float* scale, int64_t n
 
 template <typename V, typename T, bool SCALED>
 void launch_csr(mxs_ctx* ctx, const mxs_matrix* A, T alpha, const T* x, T beta, T* y,
-                const int32_t* skip, void* scratch, size_t bytes) {
+                const int32_t* skip, void* scratch, size_t bytes, bool single) {
   const CsrPart& P = A->csr;
-  if (P.bin.on()) {
+  if (P.bin.on() && !(P.near && single)) {
     // without room for the partial sums: a wave a row, the kernel that needs
     // neither scratch nor tables (power-law rows, s = 1.79, 2^20 columns, from
     // the caches: FP64 242 us against 59 in two passes, FP32 192 against 37)
@@ -1971,7 +1972,7 @@ void launch_ell(mxs_ctx* ctx, const mxs_matrix* A, T alpha, const T* x, T beta, 
 
 template <typename V, typename T, bool SCALED>
 void launch_typed(mxs_ctx* ctx, const mxs_matrix* A, T alpha, const T* x, T beta, T* y,
-                  const int32_t* skip, void* scratch, size_t bytes) {
+                  const int32_t* skip, void* scratch, size_t bytes, bool single) {
   if constexpr (!SCALED) {
     const DiagPart& D = A->fmt == MXS_COO ? A->coo.diag : A->ell.diag;
     if (A->fmt != MXS_CSR && D.on()) {
@@ -1981,7 +1982,7 @@ void launch_typed(mxs_ctx* ctx, const mxs_matrix* A, T alpha, const T* x, T beta
   }
   switch (A->fmt) {
     case MXS_CSR:
-      launch_csr<V, T, SCALED>(ctx, A, alpha, x, beta, y, skip, scratch, bytes);
+      launch_csr<V, T, SCALED>(ctx, A, alpha, x, beta, y, skip, scratch, bytes, single);
       break;
     case MXS_COO:
       launch_coo<V, T, false>(ctx, A->coo, A->n, alpha, x, beta, y, skip, scratch, bytes);
@@ -2004,8 +2005,9 @@ void launch_typed(mxs_ctx* ctx, const mxs_matrix* A, T alpha, const T* x, T beta
 
 namespace {
 
-const BinPart* bins_of(const mxs_matrix* A) {
-  if (A->fmt == MXS_CSR && A->csr.bin.on()) return &A->csr.bin;
+// the bins that products of A run over
+const BinPart* bins_of(const mxs_matrix* A, bool single) {
+  if (A->fmt == MXS_CSR && A->csr.bin.on() && !(A->csr.near && single)) return &A->csr.bin;
   if ((A->fmt == MXS_COO || A->fmt == MXS_HYB) && A->coo.bin.on()) return &A->coo.bin;
   return nullptr;
 }
@@ -2029,28 +2031,30 @@ size_t chunk_scratch_bytes(const mxs_matrix* A) {
 
 mxs_status launch_spmv_scratch(mxs_ctx* ctx, const mxs_matrix* A, const void* alpha,
                                const void* x, const void* beta, void* y, const int32_t* skip,
-                               void* scratch, size_t bytes) {
+                               void* scratch, size_t bytes, bool single) {
   if (A->n == 0) return MXS_OK;
   if (A->dt == MXS_F64) {
     launch_typed<double, double, false>(ctx, A, *(const double*)alpha, (const double*)x,
-                                        *(const double*)beta, (double*)y, skip, scratch,
-                                        bytes);
+                                        *(const double*)beta, (double*)y, skip, scratch, bytes,
+                                        single);
   } else if (A->dt == MXS_F32) {
     launch_typed<float, float, false>(ctx, A, *(const float*)alpha, (const float*)x,
-                                      *(const float*)beta, (float*)y, skip, scratch, bytes);
+                                      *(const float*)beta, (float*)y, skip, scratch, bytes,
+                                      single);
   } else if (A->dt == MXS_C128) {
     using Z = cplx<double>;
     if (A->fmt != MXS_CSR) return fail(ctx, MXS_UNSUPPORTED, "complex values are CSR only");
     launch_csr<Z, Z, false>(ctx, A, *(const Z*)alpha, (const Z*)x, *(const Z*)beta, (Z*)y, skip,
-                            scratch, bytes);
+                            scratch, bytes, single);
   } else if (A->dt == MXS_C64) {
     using Z = cplx<float>;
     if (A->fmt != MXS_CSR) return fail(ctx, MXS_UNSUPPORTED, "complex values are CSR only");
     launch_csr<Z, Z, false>(ctx, A, *(const Z*)alpha, (const Z*)x, *(const Z*)beta, (Z*)y, skip,
-                            scratch, bytes);
+                            scratch, bytes, single);
   } else {
     launch_typed<_Float16, float, true>(ctx, A, *(const float*)alpha, (const float*)x,
-                                        *(const float*)beta, (float*)y, skip, scratch, bytes);
+                                        *(const float*)beta, (float*)y, skip, scratch, bytes,
+                                        single);
   }
   MXS_HIP_TRY(ctx, hipGetLastError());
   return MXS_OK;
@@ -2149,14 +2153,14 @@ mxs_status grow_scratch(mxs_ctx* ctx, size_t need, bool* ok) {
   return MXS_OK;
 }
 
-// Scratch for a product of A: all partial sums of the two passes, else those
-// of their largest batch, else what A's ordinary kernel takes and `extra`
-// bytes (MXS_OOM without these).  A stream under capture gets what is there or
+// Scratch for a product of A: all partial sums of the two passes over B (NULL:
+// it does not run in two), else those of their largest batch, else what A's
+// ordinary kernel takes and `extra` bytes (MXS_OOM without these).  A stream under capture gets what is there or
 // MXS_OOM: memory that cannot be had now may be there outside the capture.
-mxs_status reserve_scratch(mxs_ctx* ctx, const mxs_matrix* A, size_t extra) {
+mxs_status reserve_scratch(mxs_ctx* ctx, const mxs_matrix* A, const BinPart* B, size_t extra) {
   size_t need = chunk_scratch_bytes(A) + extra;
   bool ok = false;
-  if (const BinPart* B = bins_of(A)) {
+  if (B) {
     const size_t xb = A->dt == MXS_F64 ? 8 : 4;
     const size_t whole = (size_t)B->parts * xb, least = (size_t)B->least * xb;
     if (whole <= ctx->spmv_ws.bytes) return MXS_OK;
@@ -2191,7 +2195,7 @@ int launch_spmv_dot(mxs_ctx* ctx, const mxs_matrix* A, const void* x, void* y,
     return 0;
   // the merge path without panels also keeps one dot partial per chunk
   const size_t extra = P.merge && P.panels <= 1 ? (size_t)P.nchunks * sizeof(double) : 0;
-  if (reserve_scratch(ctx, A, extra) != MXS_OK) return 0;
+  if (reserve_scratch(ctx, A, P.bin.on() ? &P.bin : nullptr, extra) != MXS_OK) return 0;
   void* sc = ctx->spmv_ws.ptr;
   int g = 0;
   if (A->dt == MXS_F64)
@@ -2208,10 +2212,10 @@ int launch_spmv_dot(mxs_ctx* ctx, const mxs_matrix* A, const void* x, void* y,
 
 // With the context's own scratch.
 mxs_status launch_spmv(mxs_ctx* ctx, const mxs_matrix* A, const void* alpha, const void* x,
-                       const void* beta, void* y, const int32_t* skip) {
-  if (mxs_status st = reserve_scratch(ctx, A, 0)) return st;
+                       const void* beta, void* y, const int32_t* skip, bool single) {
+  if (mxs_status st = reserve_scratch(ctx, A, bins_of(A, single), 0)) return st;
   return launch_spmv_scratch(ctx, A, alpha, x, beta, y, skip, ctx->spmv_ws.ptr,
-                             ctx->spmv_ws.bytes);
+                             ctx->spmv_ws.bytes, single);
 }
 
 }  // namespace mxs
@@ -2221,7 +2225,7 @@ extern "C" mxs_status mxs_spmv(mxs_ctx* ctx, const void* alpha, const mxs_matrix
   if (!ctx || !A || !alpha || !beta) return MXS_INVALID_ARG;
   if (A->n > 0 && !y) return mxs::fail(ctx, MXS_INVALID_ARG, "y is NULL");
   if (A->nnz > 0 && !x) return mxs::fail(ctx, MXS_INVALID_ARG, "x is NULL");
-  return mxs::launch_spmv(ctx, A, alpha, x, beta, y, nullptr);
+  return mxs::launch_spmv(ctx, A, alpha, x, beta, y, nullptr, true);
 }
 
 extern "C" mxs_status mxs_spmv_noalloc(mxs_ctx* ctx, const void* alpha, const mxs_matrix* A,
@@ -2243,5 +2247,5 @@ extern "C" mxs_status mxs_spmv_noalloc(mxs_ctx* ctx, const void* alpha, const mx
   void* p = mxs::noalloc_scratch(ctx->device);
   if (!p) return mxs::fail(ctx, MXS_HIP, "product scratch of device %d not set up", ctx->device);
   return mxs::launch_spmv_scratch(ctx, A, alpha, x, beta, y, nullptr, p,
-                                  mxs::kNoAllocScratchBytes);
+                                  mxs::kNoAllocScratchBytes, true);
 }

@@ -165,3 +165,86 @@ def test_more_bins_than_dot_partials(env, orc, solver):
     xh = x.cpu().numpy()
     assert orc.true_relres(A, b, xh) <= 1e-10 + _slack(orc, A, b, xh)
     M.close()
+
+
+def _band(n, per, half, seed):
+    """Rows of `per` entries, one in each equal share of the 2 half + 1 columns
+    about the diagonal."""
+    g = I.rng(seed)
+    share = (2 * half + 1) // per
+    base = np.clip(np.arange(n) - half, 0, n - 2 * half - 1)
+    col = base[:, None] + np.arange(per) * share + g.integers(0, share, (n, per))
+    return I.CSRMatrix(n, n, np.arange(0, n * per + 1, per, dtype=np.int32),
+                       col.reshape(-1).astype(np.int32), g.uniform(-1, 1, n * per))
+
+
+def _unknowns3(N):
+    """Three unknowns at each node of a 27-point grid (rows of 81)."""
+    P = I.stencil27(N)
+    lens = np.repeat(P.row_lengths() * 3, 3)
+    rp = np.zeros(3 * P.n + 1, np.int64)
+    np.cumsum(lens, out=rp[1:])
+    cols = (P.col[:, None].astype(np.int64) * 3 + np.arange(3)).ravel()
+    node = np.repeat(np.arange(P.n), 3)
+    off = np.arange(rp[-1]) - np.repeat(rp[:-1], lens)
+    col = cols[np.repeat(P.rowptr[:-1].astype(np.int64)[node] * 3, lens) + off]
+    v = np.where(col == np.repeat(np.arange(3 * P.n), lens), 90.0, -1.0)
+    return I.CSRMatrix(3 * P.n, 3 * P.n, rp.astype(np.int32), col.astype(np.int32), v)
+
+
+@pytest.mark.parametrize("name,near", [("band_200", True), ("band_600", True),
+                                       ("band_2000", False), ("grid", True), ("scattered", False)])
+def test_rows_whose_columns_are_near(env, orc, name, near):
+    """FP64 products of rows that share their columns stay on the merge path:
+    they are its bits (chunks of 512 entries), where two passes add a row's
+    products in runs of 8; FP32 ones run in two passes either way."""
+    mxs, ctx, torch = env
+    A = (_unknowns3(23) if name == "grid" else _spd() if name == "scattered"
+         else _band(40000, 80, int(name[5:]), 81))
+    A.val[:] = I.rng(82).uniform(-1, 1, A.nnz)
+    M = mxs.Matrix.from_host(ctx, A)
+    for dt in ("f64", "f32"):
+        tdt = torch.float64 if dt == "f64" else torch.float32
+        x = I.uniform_vector(A.n, 83)
+        val = A.val
+        if dt == "f32":
+            x, val = (v.astype(np.float32).astype(np.float64) for v in (x, val))
+        R = I.CSRMatrix(A.n, A.n, A.rowptr, A.col, val)
+        xd = torch.from_numpy(x).to(tdt).cuda()
+        ys = []
+        for opts in ({}, dict(csr_kernel="merge")):
+            B = M.convert("csr", dt, **opts)
+            y, z = (torch.full((A.n,), float("nan"), dtype=tdt, device="cuda") for _ in range(2))
+            mxs.spmv(ctx, B, xd, y)
+            mxs.spmv(ctx, B, xd, z, noalloc=True)
+            assert torch.equal(y, z)
+            ys.append(y)
+            B.close()
+        err = np.abs(ys[0].cpu().numpy().astype(np.float64) - orc.spmv_csr(R, x))
+        assert (err <= (1e-13 if dt == "f64" else 1e-5) * orc.absrow(R, x) + 1e-30).all()
+        assert torch.equal(*ys) == (near and dt == "f64")
+    M.close()
+
+
+@pytest.mark.parametrize("kind", ["cg", "pcg", "bicgstab", "cgs", "gmres", "pipecg"])
+def test_solvers_on_near_rows(env, orc, kind):
+    """A solver's products (with and without dots) in two passes, a product by
+    itself on the merge path, with the context's scratch growing in between."""
+    mxs, _, torch = env
+    ctx = mxs.Context(0)
+    A = _unknowns3(23)
+    b = I.uniform_vector(A.n, 84)
+    M = mxs.Matrix.from_host(ctx, A)
+    P = mxs.Precond(ctx, M, "jacobi") if kind == "pcg" else None
+    x = torch.zeros(A.n, dtype=torch.float64, device="cuda")
+    y = torch.zeros_like(x)
+    mxs.spmv(ctx, M, torch.from_numpy(b).cuda(), y)
+    err = np.abs(y.cpu().numpy() - orc.spmv_csr(A, b))
+    assert (err <= 1e-13 * orc.absrow(A, b)).all()
+    mxs.solve(ctx, "cg" if P else kind, M, torch.from_numpy(b).cuda(), x, tol=1e-10, precond=P)
+    xh = x.cpu().numpy()
+    assert orc.true_relres(A, b, xh) <= 1e-10 + _slack(orc, A, b, xh)
+    if P:
+        P.close()
+    M.close()
+    ctx.close()
