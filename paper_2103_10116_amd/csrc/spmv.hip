@@ -28,7 +28,8 @@
 // HYB  -- ELL kernel for the regular part, then the COO kernel in
 //         accumulate mode for the overflow.
 // Matrices of few diagonals (stencils) in any of these formats run k_diag over
-// a copy of their values by diagonals unless a kernel was asked for.
+// a copy of their values by diagonals unless a kernel was asked for or the rows
+// are too few for their diagonals (diag_pays).
 // Irregular CSR, COO and HYB matrices large enough to gain from it run the
 // two-pass product of binned.hip unless a kernel was asked for (FP64 CSR whose
 // neighbouring rows share their columns: only inside the solvers).
@@ -1415,6 +1416,39 @@ template <typename V>
 constexpr bool kDiagValue = std::is_same_v<V, double> || std::is_same_v<V, float> ||
                             std::is_same_v<V, _Float16>;
 
+// Rounds of a row's diagonals, one after the other (see launch_diag).
+int diag_rounds(const DiagPart& P) {
+  const int u = P.threes || P.D % 9 == 0 ? 9 : P.D % 7 == 0 ? 7 : P.D % 5 == 0 ? 5 : 8;
+  return (P.D + u - 1) / u;
+}
+
+// Whether the product of a matrix kept by diagonals runs over them.  A wave's
+// rounds follow each other, about 1 us each, which the format's own kernel,
+// with its entries over more waves, undercuts while the rows are few.  Lines
+// measured on 2 to 64 diagonals of 2000 to 192000 rows, us from HBM (repeated),
+// over diagonals / the format's kernel:
+//  CSR FP64, 6500 rows a round: 27 diagonals of 16000 rows 8.0 / 7.2, of 32000
+//    8.0 / 8.4; 64 of 32000 14.2 / 13.6 (10.0 / 8.6), of 48000 14.8 / 16.3;
+//  with dots, which that kernel does not form: CG an iteration on 27 of 10000
+//    14.8 / 16.7, on 64 of 24000 21.3 / 20.3, of 32000 21.5 / 21.6;
+//  CSR FP32 and FP16, 12000: FP32 48 of 64000 11.6 / 11.2 (8.1 / 6.1), of 96000
+//    12.2 / 14.7 (8.1 / 10.1); 64 of 64000 13.6 / 13.6 (9.8 / 8.5), of 96000 14.4 /
+//    17.8 (10.0 / 13.2); 27 of 16000 7.5 / 6.9, of 32000 7.2 / 7.6;
+//  COO, from 6 rounds on 4500: FP64 48 of 16000 12.1 / 11.4, of 32000 12.5 /
+//    13.4; 64 of 24000 14.1 / 13.2 (9.9 / 8.4), of 48000 14.8 / 17.4;
+//  ELL (and HYB, which is its ELL part then): from 4 diagonals on; 3 of 2^20 rows
+//    FP32 (6.7 / 5.8), FP64 (10.0 / 9.8), 2 of 2^22 FP32 29.7 / 26.1 (20.0 /
+//    17.3); many of few rows gain from HBM what FP32 loses repeated (48 of 6000
+//    11.3 / 15.8 and 7.9 / 5.8; FP64 12.2 / 30.4 and 7.9 / 10.3).
+bool diag_pays(const mxs_matrix* A, const DiagPart& P, bool dots) {
+  const int64_t rounds = diag_rounds(P);
+  if (A->fmt == MXS_ELL || A->fmt == MXS_HYB) return P.D >= 4;
+  if (rounds == 1) return true;
+  if (A->fmt == MXS_COO) return rounds < 6 || A->n >= 4500 * rounds;
+  if (A->dt != MXS_F64) return A->n >= 12000 * rounds;
+  return A->n >= (dots ? 5000 * (rounds - 2) : 6500 * rounds);
+}
+
 // nv > 0: at most kDotPartials work-groups, whose number is returned.  Products
 // that form dots keep ordinary loads whatever the size (CG on 27-point 128^3,
 // 453 MB of values: 136 us an iteration, 128 with non-temporal ones; 7-point
@@ -1801,7 +1835,7 @@ void launch_csr(mxs_ctx* ctx, const mxs_matrix* A, T alpha, const T* x, T beta, 
     return;
   }
   if constexpr (kDiagValue<V>) {
-    if (P.diag.on()) {
+    if (P.diag.on() && diag_pays(A, P.diag, false)) {
       launch_diag<V, T, SCALED>(ctx, A, P.diag, P.scale, alpha, x, beta, y, skip);
       return;
     }
@@ -1975,7 +2009,7 @@ void launch_typed(mxs_ctx* ctx, const mxs_matrix* A, T alpha, const T* x, T beta
                   const int32_t* skip, void* scratch, size_t bytes, bool single) {
   if constexpr (!SCALED) {
     const DiagPart& D = A->fmt == MXS_COO ? A->coo.diag : A->ell.diag;
-    if (A->fmt != MXS_CSR && D.on()) {
+    if (A->fmt != MXS_CSR && D.on() && diag_pays(A, D, false)) {
       launch_diag<V, T, false>(ctx, A, D, nullptr, alpha, x, beta, y, skip);
       return;
     }
@@ -2111,7 +2145,7 @@ int launch_dot_typed(mxs_ctx* ctx, const mxs_matrix* A, const T* x, T* y, const 
                                  skip, scratch, ctx->spmv_ws.bytes, dpart, w ? w : x, nv);
     return (int)P.bin.nbins;
   }
-  if (P.diag.on())
+  if (P.diag.on() && diag_pays(A, P.diag, true))
     return launch_diag<V, T, SCALED>(ctx, A, P.diag, P.scale, T(1), x, T(0), y, skip, w ? w : x,
                                      dpart, nv);
   if (P.rows_lds && P.nblocks > 0) {
@@ -2189,9 +2223,9 @@ int launch_spmv_dot(mxs_ctx* ctx, const mxs_matrix* A, const void* x, void* y,
                     const int32_t* skip, double* dpart, const void* w, int nv) {
   if (A->fmt != MXS_CSR || A->n == 0 || A->n != A->ncols || nv < 1 || nv > 2) return 0;
   const CsrPart& P = A->csr;
-  if (!P.diag.on() && !(P.rows_lds && P.nblocks > 0) && !(P.merge && P.nchunks > 0)) return 0;
-  if (!P.bin.on() && !P.diag.on() && !(P.rows_lds && P.nblocks > 0) &&
-      ((w && w != x) || nv != 1))
+  const bool diag = P.diag.on() && diag_pays(A, P.diag, true);
+  if (!diag && !(P.rows_lds && P.nblocks > 0) && !(P.merge && P.nchunks > 0)) return 0;
+  if (!P.bin.on() && !diag && !(P.rows_lds && P.nblocks > 0) && ((w && w != x) || nv != 1))
     return 0;
   // the merge path without panels also keeps one dot partial per chunk
   const size_t extra = P.merge && P.panels <= 1 ? (size_t)P.nchunks * sizeof(double) : 0;

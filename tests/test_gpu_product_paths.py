@@ -248,3 +248,87 @@ def test_solvers_on_near_rows(env, orc, kind):
         P.close()
     M.close()
     ctx.close()
+
+
+def _diagonals(n, D, seed):
+    """D diagonals, ten apart (no threes), all entries inside the matrix."""
+    c = np.arange(n)[:, None] + (np.arange(D) - D // 2) * 10
+    on = (c >= 0) & (c < n)
+    rp = np.zeros(n + 1, np.int64)
+    np.cumsum(on.sum(1), out=rp[1:])
+    return I.CSRMatrix(n, n, rp.astype(np.int32), c[on].astype(np.int32),
+                       I.rng(seed).uniform(-1, 1, int(rp[-1])))
+
+
+# rows on either side of each line: rounds of 9, 7, 5 or 8 diagonals times 6500
+# (CSR FP64), 12000 (CSR FP32, FP16) or, from 6 rounds on, 4500 (COO); ELL by the
+# diagonals
+ROUNDS = [("csr", "f64", 27, 19499, False), ("csr", "f64", 27, 19500, True),
+          ("csr", "f64", 64, 51999, False), ("csr", "f64", 64, 52000, True),
+          ("csr", "f64", 9, 16000, True), ("csr", "f32", 13, 23999, False),
+          ("csr", "f32", 13, 24000, True), ("csr", "f16", 27, 35999, False),
+          ("csr", "f16", 27, 36000, True), ("coo", "f64", 48, 26999, False),
+          ("coo", "f64", 48, 27000, True), ("coo", "f32", 64, 35999, False),
+          ("coo", "f32", 64, 36000, True), ("coo", "f64", 32, 5000, True),
+          ("ell", "f64", 3, 60000, False), ("ell", "f32", 4, 50000, True),
+          ("hyb", "f64", 3, 60000, False), ("hyb", "f64", 4, 50000, True)]
+
+
+@pytest.mark.parametrize("fmt,dt,D,n,over", ROUNDS)
+def test_diagonals_of_few_rows(env, orc, fmt, dt, D, n, over):
+    """Where the rows are few for their diagonals the format's own kernel runs:
+    its bits, which the order of the sums over diagonals does not give."""
+    mxs, ctx, torch = env
+    A = _diagonals(n, D, 91)
+    assert A.nnz >= 1 << 17
+    M = mxs.Matrix.from_host(ctx, A)
+    opts = {"csr": dict(csr_kernel="rows_lds" if D <= 8 or dt != "f64" else "products"),
+            "coo": dict(coo_kernel="lds")}.get(fmt, dict(waves_per_group=4))
+    x, val = I.uniform_vector(n, 92), A.val
+    if dt != "f64":
+        x, val = (v.astype(np.float32).astype(np.float64) for v in (x, val))
+    if dt == "f16":
+        _, h, s = orc.rowscale_f16(A)
+        val = orc.f16_bits_to_f64(h) * np.repeat(s.astype(np.float64), A.row_lengths())
+    R = I.CSRMatrix(n, n, A.rowptr, A.col, val)
+    tdt = torch.float64 if dt == "f64" else torch.float32
+    xd = torch.from_numpy(x).to(tdt).cuda()
+    ys, kept = [], []
+    for o in ({}, opts):
+        B = M.convert(fmt, dt, **o)
+        y, z = (torch.full((n,), float("nan"), dtype=tdt, device="cuda") for _ in range(2))
+        mxs.spmv(ctx, B, xd, y)
+        mxs.spmv(ctx, B, xd, z, noalloc=True)
+        assert torch.equal(y, z)
+        ys.append(y)
+        kept.append(B.info()["bytes"])
+        B.close()
+    assert kept[0] > kept[1]                               # the copy by diagonals
+    err = np.abs(ys[0].cpu().numpy().astype(np.float64) - orc.spmv_csr(R, x))
+    assert (err <= (1e-13 if dt == "f64" else 1e-5) * orc.absrow(R, x) + 1e-30).all()
+    assert torch.equal(*ys) == (not over)
+    M.close()
+
+
+@pytest.mark.parametrize("D,n", [(64, 4000), (64, 31000), (32, 10001), (27, 6000)])
+@pytest.mark.parametrize("kind", ["cg", "pcg", "bicgstab", "cgs", "gmres", "pipecg"])
+def test_solvers_on_diagonals_of_few_rows(env, orc, kind, D, n):
+    """Products with dots over diagonals and plain ones by the format's kernel,
+    and both by the latter (rows below the lines of both)."""
+    mxs, ctx, torch = env
+    A = _diagonals(n, D, 93)
+    # symmetric: entry (i, j) and (j, i) by the same function of i + j
+    rows = np.repeat(np.arange(n), A.row_lengths())
+    A.val[:] = np.where(rows == A.col, 2.0 * D, -np.abs(np.sin(rows + A.col.astype(np.float64))))
+    if D % 2 == 0:                                         # one diagonal without a mirror
+        A.val[A.col == rows - D // 2 * 10] = 0.0
+    b = I.uniform_vector(n, 94)
+    M = mxs.Matrix.from_host(ctx, A)
+    P = mxs.Precond(ctx, M, "jacobi") if kind == "pcg" else None
+    x = torch.zeros(n, dtype=torch.float64, device="cuda")
+    mxs.solve(ctx, "cg" if P else kind, M, torch.from_numpy(b).cuda(), x, tol=1e-10, precond=P)
+    xh = x.cpu().numpy()
+    assert orc.true_relres(A, b, xh) <= 1e-10 + _slack(orc, A, b, xh)
+    if P:
+        P.close()
+    M.close()
