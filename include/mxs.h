@@ -187,8 +187,10 @@ typedef struct {
                               In the same way matrices of at least 2^17 entries on at most 64
                               diagonals (rows of at most 64 entries, at most 255 different sets of
                               diagonals, at most a fifth of them holes) run, in any format, over a
-                              copy of their values by diagonals without column indices.  Where
-                              there is no memory for such a copy the matrix is set up without it. */
+                              copy of their values by diagonals without column indices (but by the
+                              format's kernel where the rows are few for many diagonals, or an ELL
+                              matrix has less than 4).  Where there is no memory for such a copy the
+                              matrix is set up without it. */
 
 #define MXS_COO_AUTO 0 /* RUNS for FP32/FP16 values when no row has more than 16 entries in
                           the part, else LDS */

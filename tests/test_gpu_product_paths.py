@@ -262,7 +262,7 @@ def _diagonals(n, D, seed):
 
 # rows on either side of each line: rounds of 9, 7, 5 or 8 diagonals times 6500
 # (CSR FP64), 12000 (CSR FP32, FP16) or, from 6 rounds on, 4500 (COO); ELL by the
-# diagonals
+# diagonals (three terms add up alike in both kernels: their rows pin the values)
 ROUNDS = [("csr", "f64", 27, 19499, False), ("csr", "f64", 27, 19500, True),
           ("csr", "f64", 64, 51999, False), ("csr", "f64", 64, 52000, True),
           ("csr", "f64", 9, 16000, True), ("csr", "f32", 13, 23999, False),
