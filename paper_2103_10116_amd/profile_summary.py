@@ -173,7 +173,7 @@ def counters(out: str, command: str, paths, prefixes=("k_",)) -> None:
 
 
 def load_traffic(path: str) -> dict:
-    """{(kernel, grid): bytes} if the file matches the current spmv.hip."""
+    """{(kernel, grid): bytes} if the file matches the current sources of the products."""
     try:
         lines = open(path).read().splitlines()
     except OSError:
